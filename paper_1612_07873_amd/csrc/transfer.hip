@@ -8,13 +8,11 @@
 // One work-group per (aggregate, chirality), FP64, working set in global
 // memory (it is read from L2).
 //
-// Apply:
+// Apply, for all members of a batch together:
 //   prolong  (P u)(x)_f = sum_k V(x)_{f,k} u(xc(x))_{chi(f)*Nvec + k}
-//            a gather, one thread per fine degree of freedom;
 //   restrict (R psi)(xc)_{chi*Nvec + k} = sum_{x in xc, chi(f) = chi} conj(V(x)_{f,k}) psi(x)_f
-//            one work-group per aggregate, each thread owning one coarse
-//            component and a slice of the aggregate, partial sums combined in
-//            LDS in a fixed order: no atomics, bitwise repeatable.
+// both as dense products per (aggregate, chirality) on the matrix cores, every
+// sum in a fixed order: no atomics, bitwise repeatable.
 // The basis is kept as [V][dof][Nvec] (row f of site x holds the Nvec
 // coefficients of its chirality) in the storage precision, plus an FP64 copy
 // for the Galerkin build.  The 16-bit storage keeps each complex entry as an
@@ -23,6 +21,7 @@
 #include "codes16.h"
 #include "handles.h"
 
+#include <algorithm>
 #include <vector>
 
 namespace qmg {
@@ -132,35 +131,392 @@ __global__ void k_to_h16(uint32_t* __restrict__ o, const double2* __restrict__ i
     o[g] = enc_pair<FMT_H16>((float)i[g].x, (float)i[g].y);
 }
 
-// A stored basis entry as a complex number of the arithmetic precision R:
-// BT = cpx<R> (complex128 or complex64 storage) or a 32-bit FP16 pair.
-template <typename R> __device__ __forceinline__ cpx<R> bval(const cpx<R>& b) { return b; }
-template <typename R> __device__ __forceinline__ cpx<R> bval(const uint32_t& w) {
-    const cpx<float> v = dec_pair<FMT_H16>(w);
-    return cpx<R>{(R)v.re, (R)v.im};
+// Both directions run on the matrix cores, in the arithmetic precision of the
+// fields (v_mfma_f32_16x16x4_f32 / v_mfma_f64_16x16x4_f64: one real per lane
+// and operand, products and sums in that precision).  Per aggregate and
+// chirality the transfer is one dense product with the aggregate's block of
+// the basis, a real matrix of rows (site, f) and 2 nvec columns (k, re/im);
+// the fields' columns are (member, re/im), so 8 members fill a tile of 16
+// columns and the basis is read once for up to 32 members.  The bound is the
+// basis stream: complex64, 16^3x32, nvec 24, twelve members, 302 MB of basis
+// and 151 MB of fields.  One kernel per member (each re-reading the basis)
+// took 559 us (restriction) and 752 us (prolongation); these take 108 and 117.
+// Every column of a product is summed in the same order whatever the number of
+// members, so with a complex64 basis a member of a batch equals the single call
+// bitwise.
+template <typename R> struct Mm;
+template <> struct Mm<float> {
+    typedef float V4 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ V4 mac(float a, float b, V4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    // row of a lane's element q (column lane % 16), g = lane / 16
+    static __device__ __forceinline__ int row(int g, int q) { return 4 * g + q; }
+};
+template <> struct Mm<double> {
+    typedef double V4 __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ V4 mac(double a, double b, V4 c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int row(int g, int q) { return 4 * q + g; }
+};
+
+// The (aggregate, chirality) of work-group i: work-groups are dealt to the 8
+// XCDs round-robin, and the two chiralities of an aggregate, whose rows of a
+// field share cache lines, go to the same one.  -1 past the last aggregate.
+__device__ __forceinline__ int64_t agg_of(int64_t i, int64_t Vc, int& chi) {
+    const int64_t xc = (i >> 4) * 8 + (i & 7);
+    chi = (int)(i >> 3) & 1;
+    return xc < Vc ? xc : -1;
 }
+static int64_t agg_grid(int64_t Vc) { return (Vc + 7) / 8 * 16; }
+
+// n reals of a basis row as stored (ST: the storage's real type), decoded only
+// when they are used: a conversion next to the load would wait for it and end
+// the prefetch.  FP16 is kept as words of two.  Plain reals are read by scalar
+// loads, which the compiler joins into the widest that stay inside the n (a
+// three-element vector type would be read as four, past the end of the basis).
+template <typename ST, int n> struct Raw {
+    ST v[n];
+    template <typename R> __device__ __forceinline__ R get(int i) const { return (R)v[i]; }
+    __device__ __forceinline__ void zero() {
+#pragma unroll
+        for (int i = 0; i < n; ++i) v[i] = 0;
+    }
+};
+template <int n> struct Raw<_Float16, n> {
+    uint32_t v[(n + 1) / 2];
+    template <typename R> __device__ __forceinline__ R get(int i) const {
+        return (R)h16_to_f32((uint16_t)(i & 1 ? v[i >> 1] >> 16 : v[i >> 1] & 0xffffu));
+    }
+    __device__ __forceinline__ void zero() {
+#pragma unroll
+        for (int i = 0; i < (n + 1) / 2; ++i) v[i] = 0;
+    }
+};
+
+// The T columns of a basis row that lane i of 16 holds in the restriction:
+// T i + t, so that a lane's columns are contiguous; with FP16 the pairs
+// 2 i, 2 i + 1 of each 32 columns and then, for an odd T, column 16 (T - 1) + i,
+// which keeps every word aligned.
+template <typename ST, int T> __device__ __forceinline__ int basis_col(int i, int t) {
+    if constexpr (sizeof(ST) == 2) return T % 2 && t == T - 1 ? 16 * t + i : 32 * (t >> 1) + 2 * i + (t & 1);
+    else return T * i + t;
+}
+// Those columns of a row (non-temporal: read once per application); past
+// the last column, the last one or pair again.
+template <bool FULL, typename ST, int T>
+__device__ __forceinline__ void ld_cols(Raw<ST, T>& v, const ST* row, int i, int cols) {
+    if constexpr (sizeof(ST) == 2) {
+        const uint32_t* w = reinterpret_cast<const uint32_t*>(row);
+#pragma unroll
+        for (int t = 0; t < T / 2; ++t) {
+            const int c = 16 * t + i;
+            v.v[t] = __builtin_nontemporal_load(w + (FULL ? c : min(c, (cols >> 1) - 1)));
+        }
+        if constexpr (T % 2) {
+            const int c = 16 * (T - 1) + i;
+            v.v[T / 2] = __builtin_nontemporal_load(reinterpret_cast<const uint16_t*>(row) + (FULL ? c : min(c, cols - 1)));
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < T; ++t) v.v[t] = __builtin_nontemporal_load(row + (FULL ? T * i + t : min(T * i + t, cols - 1)));
+    }
+}
+// n (even) consecutive reals from column c0 on; zero past the last column
+template <bool FULL, typename ST, int n>
+__device__ __forceinline__ void ld_run(Raw<ST, n>& v, const ST* row, int c0, int cols) {
+    if constexpr (sizeof(ST) == 2) {
+        const uint32_t* w = reinterpret_cast<const uint32_t*>(row + c0);
+#pragma unroll
+        for (int i = 0; i < n / 2; ++i) v.v[i] = FULL || c0 + 2 * i < cols ? w[i] : 0u;
+    } else {
+#pragma unroll
+        for (int i = 0; i < n; ++i) v.v[i] = FULL || c0 + i < cols ? row[c0 + i] : ST(0);
+    }
+}
+
+// Restriction: S(m, n) = sum over the rows r of an (aggregate, chirality) of
+// basis(r, m) field(r, n), m = (k, re/im), n = (member, re/im); the coarse
+// component is then S(k re, j re) + S(k im, j im) + i [S(k re, j im) - S(k im, j re)].
+// One work-group per (aggregate, chirality); its wave w takes the chunks of 16
+// rows w, w + 8, ...  Each chunk's sum (four products of depth four) is added
+// to the wave's total and the waves' totals are added in LDS, all in a fixed
+// order.  A lane holds T consecutive columns of its row (T = 3 at nvec 24: a
+// wave reads four whole rows, 768 contiguous bytes, per load), so tile t of S
+// covers the columns basis_col(i, t).  A chunk's fields pass through the wave's own
+// part of LDS as [row][n]; no wave waits for another before the end, and the
+// next chunk's basis rows (non-temporal) and fields are in flight while this
+// one is multiplied.  (Chunks of 128 rows staged by the whole work-group, two
+// barriers each, took 139 us against 108 for twelve members, complex64.)
+// FULL: the 16 T columns are all there (nvec a multiple of 8, at most 32);
+// otherwise, and for the blocks of 32 vectors of a larger nvec (grid dimension
+// z), columns past the last one read it again and are not stored.
+constexpr int kRestrictWaves = 8;
+constexpr int restrict_ld(int NT) { return NT == 1 ? 16 : 16 * NT + 16; }   // LDS row of a chunk: the four row groups of a read in different banks
+
+template <typename R, typename ST, int T, int NT, bool FULL>
+__global__ __launch_bounds__(64 * kRestrictWaves, T <= 3 && NT <= 2 && sizeof(R) == 4 ? 4 : 2) void k_restrict(
+    cpx<R>* __restrict__ out, const ST* __restrict__ B, const cpx<R>* __restrict__ in, const int* __restrict__ members,
+    int dof, int nvec, int bsites, int64_t V, int64_t Vc, int nrhs) {
+    using V4 = typename Mm<R>::V4;
+    constexpr int W = kRestrictWaves, U = 4, LDF = restrict_ld(NT), P = 2 * NT;
+    extern __shared__ __align__(16) unsigned char smem[];
+    R* sh = reinterpret_cast<R*>(smem);                // [wave][16][LDF], then [wave][16 T][16]
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int i16 = l & 15, g = l >> 4;
+    int chi;
+    const int64_t xc = agg_of(blockIdx.x, Vc, chi);
+    if (xc < 0) return;   // the whole work-group
+    const int half = dof >> 1;
+    const int k0 = (int)blockIdx.z * 32;
+    const int cols = 2 * (FULL ? nvec : (nvec - k0 < 32 ? nvec - k0 : 32));
+    const int j0 = (int)blockIdx.y * 8 * NT;
+    const int nj = nrhs - j0 < 8 * NT ? nrhs - j0 : 8 * NT;
+    const int* mem = members + xc * bsites;
+    const int rows = bsites * half;
+    R* mine = sh + w * 16 * LDF;
+    V4 tot[T][NT];
+#pragma unroll
+    for (int r = 0; r < T; ++r)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) tot[r][t] = V4{0, 0, 0, 0};
+    // row i16 of the wave's current chunk: (site, f), stepped by 16 W rows
+    int site = (16 * w + i16) / half, f = 16 * w + i16 - site * half;
+    const int dsite = 16 * W / half, df = 16 * W - dsite * half;
+    int x = mem[site < bsites ? site : bsites - 1];    // lattice site of the row (any for a row past the end)
+    constexpr int NB = 2;   // chunks in flight, one included
+    Raw<ST, T> a[NB][U];
+    cpx<R> fv[NB][P];
+    // Basis rows 4 u + g and this lane's field entries (row i16, members g + 4 p) of the current chunk,
+    // then the site of the next chunk's row.  Rows past the end read a row of the last site, members past
+    // the last one that one.
+    auto load = [&](Raw<ST, T> (&d)[U], cpx<R> (&v)[P]) {
+        const int64_t row = (int64_t)x * dof + chi * half + f;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            ld_cols<FULL>(d[u], B + ((int64_t)__shfl((long long)row, 4 * u + g, 64) * nvec + k0) * 2, i16, cols);
+#pragma unroll
+        for (int p = 0; p < P; ++p) v[p] = in[(int64_t)(j0 + min(g + 4 * p, nj - 1)) * V * dof + row];
+        site += dsite;
+        f += df;
+        if (f >= half) { f -= half; ++site; }
+        x = mem[site < bsites ? site : bsites - 1];
+    };
+    auto step = [&](Raw<ST, T> (&d)[U], cpx<R> (&v)[P], int c, bool more) {
+        const bool live = 16 * c + i16 < rows;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            mine[i16 * LDF + 2 * (g + 4 * p)] = live ? v[p].re : R(0);
+            mine[i16 * LDF + 2 * (g + 4 * p) + 1] = live ? v[p].im : R(0);
+        }
+        if (16 * c + 16 > rows) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (16 * c + 4 * u + g >= rows) d[u].zero();
+        }
+        __builtin_amdgcn_wave_barrier();   // the wave's LDS accesses complete in order
+        V4 acc[T][NT];
+#pragma unroll
+        for (int r = 0; r < T; ++r)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[r][t] = V4{0, 0, 0, 0};
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            R b[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) b[t] = mine[(4 * u + g) * LDF + 16 * t + i16];
+#pragma unroll
+            for (int r = 0; r < T; ++r)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[r][t] = Mm<R>::mac(d[u].template get<R>(r), b[t], acc[r][t]);
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int r = 0; r < T; ++r)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) tot[r][t] += acc[r][t];
+        if (more) load(d, v);   // the chunk NB steps on
+    };
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+        if (16 * (w + k * W) < rows) load(a[k], fv[k]);
+    int c = w;
+    // whole rounds first, whose loads are unconditional: a load under a
+    // condition makes the next wait one for all loads before it
+    for (; 16 * (c + (2 * NB - 1) * W) < rows; c += NB * W) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) step(a[k], fv[k], c + k * W, true);
+    }
+    for (; 16 * c < rows; c += NB * W) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+            if (16 * (c + k * W) < rows) step(a[k], fv[k], c + k * W, 16 * (c + (k + NB) * W) < rows);
+    }
+    constexpr int M = 16 * T, LD = 16;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        if (8 * t >= nj) break;                        // the whole work-group
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < T; ++r)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) sh[(w * M + basis_col<ST, T>(Mm<R>::row(g, q), r)) * LD + i16] = tot[r][t][q];
+        __syncthreads();
+        for (int e = threadIdx.x; e < 8 * (cols >> 1); e += 64 * W) {
+            const int jj = e / (cols >> 1), k = e - jj * (cols >> 1);
+            if (8 * t + jj >= nj) continue;
+            R re = 0, im = 0;
+#pragma unroll
+            for (int v = 0; v < W; ++v) {
+                const R* p = sh + (v * M + 2 * k) * LD + 2 * jj;
+                re += p[0] + p[LD + 1];
+                im += p[1] - p[LD];
+            }
+            const int64_t o = (int64_t)(j0 + 8 * t + jj) * Vc + xc;
+            out[o * 2 * nvec + chi * nvec + k0 + k] = cpx<R>{re, im};
+        }
+    }
+}
+
+// Prolongation: row r of an (aggregate, chirality) times the coarse columns,
+//   P(r, j re) = sum_k W(k re) c(k, j).re - W(k im) c(k, j).im,
+//   P(r, j im) = sum_k W(k re) c(k, j).im + W(k im) c(k, j).re.
+// A work-group takes up to kProlongTiles tiles of 16 rows (grid dimension z
+// divides an aggregate's tiles evenly), whose places in a fine field it first
+// puts in LDS.  The coarse operand stays in registers while a wave walks its
+// tiles; lane group g (of 16 lanes) holds the KS columns g KS ... of its rows,
+// 48 contiguous bytes per lane at nvec 24, and the next tile's are loaded
+// while this one is multiplied.  Lanes of the two parts of a member exchange
+// halves, so that each stores whole complex numbers (16 bytes where the rows
+// of a chirality are even in number and `out` is so aligned: `wide`).
+// FULL: 2 nvec = 4 KS.
+template <typename R> constexpr int kProlongTiles = sizeof(R) == 4 ? 16 : 32;   // complex64 66 (32 tiles) -> 63 us, complex128 132 (32) against 147 (16)
+
+template <typename R, typename ST, int KS, int NT, bool FULL>
+__global__ __launch_bounds__(256) void k_prolong(cpx<R>* __restrict__ out, const ST* __restrict__ B,
+                                                 const cpx<R>* __restrict__ uc, const int* __restrict__ members,
+                                                 int dof, int nvec, int bsites, int64_t V, int64_t Vc, int nrhs,
+                                                 int wide) {
+    using V4 = typename Mm<R>::V4;
+    __shared__ int64_t at[16 * kProlongTiles<R>];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int i16 = l & 15, g = l >> 4, odd = l & 1;
+    int chi;
+    const int64_t xc = agg_of(blockIdx.x, Vc, chi);
+    if (xc < 0) return;   // the whole work-group
+    const int half = dof >> 1;
+    const int j0 = (int)blockIdx.y * 8 * NT;
+    const int rows = bsites * half;
+    const int tiles = (rows + 15) >> 4;
+    const int t0 = (int)((int64_t)tiles * blockIdx.z / gridDim.z), t1 = (int)((int64_t)tiles * (blockIdx.z + 1) / gridDim.z);
+    const int cols = 2 * nvec;
+    for (int e = threadIdx.x; e < 16 * (t1 - t0); e += 256) {
+        const int q = 16 * t0 + e;
+        const int site = q / half;
+        // -1 past the last row
+        at[e] = q < rows ? (int64_t)members[xc * bsites + site] * dof + chi * half + (q - site * half) : -1;
+    }
+    R b[KS][NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        int j = j0 + 8 * t + (i16 >> 1);
+        if (j >= nrhs) j = nrhs - 1;
+        const cpx<R>* c = uc + ((int64_t)j * Vc + xc) * cols + chi * nvec;
+#pragma unroll
+        for (int s = 0; s < KS; s += 2) {
+            const int e = g * KS + s;
+            cpx<R> v = {0, 0};
+            if (FULL || e < cols) v = c[e >> 1];
+            b[s][t] = odd ? v.im : v.re;
+            b[s + 1][t] = odd ? v.re : -v.im;
+        }
+    }
+    __syncthreads();
+    auto load = [&](Raw<ST, KS>& a, int tile) {
+        int64_t x = at[16 * tile + i16];
+        if (x < 0) x = at[16 * tile];   // rows past the end: the tile's first row, not stored
+        ld_run<FULL>(a, B + x * cols, g * KS, cols);
+    };
+    const int n = t1 - t0;
+    auto step = [&](Raw<ST, KS>& a, int tile) {
+        // this lane's two rows: elements 0 and 1 (even lanes) or 2 and 3 (odd lanes)
+        const int64_t o0 = at[16 * tile + Mm<R>::row(g, 2 * odd)], o1 = at[16 * tile + Mm<R>::row(g, 2 * odd + 1)];
+        V4 acc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = V4{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[t] = Mm<R>::mac(a.template get<R>(s), b[s][t], acc[t]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const R x0 = odd ? acc[t][0] : acc[t][2], x1 = odd ? acc[t][1] : acc[t][3];
+            const R y0 = __shfl_xor(x0, 1, 64), y1 = __shfl_xor(x1, 1, 64);
+            const cpx<R> v0 = odd ? cpx<R>{y0, acc[t][2]} : cpx<R>{acc[t][0], y0};
+            const cpx<R> v1 = odd ? cpx<R>{y1, acc[t][3]} : cpx<R>{acc[t][1], y1};
+            const int j = j0 + 8 * t + (i16 >> 1);
+            if (j >= nrhs) continue;
+            cpx<R>* o = out + (int64_t)j * V * dof;
+            if (sizeof(R) == 4 && wide) {
+                if (o0 >= 0) *reinterpret_cast<float4*>(o + o0) = make_float4(v0.re, v0.im, v1.re, v1.im);
+            } else {
+                if (o0 >= 0) o[o0] = v0;
+                if (o1 >= 0) o[o1] = v1;
+            }
+        }
+    };
+    // NB tiles in flight, one included; whole rounds first, whose loads are
+    // unconditional (a load under a condition makes the next wait one for all
+    // loads before it)
+    constexpr int NB = 2;
+    Raw<ST, KS> a[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+        if (w + 4 * k < n) load(a[k], w + 4 * k);
+    int tile = w;
+    for (; tile + 4 * (2 * NB - 1) < n; tile += 4 * NB) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            step(a[k], tile + 4 * k);
+            load(a[k], tile + 4 * (k + NB));
+        }
+    }
+    for (; tile < n; tile += 4 * NB) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+            if (tile + 4 * k < n) {
+                step(a[k], tile + 4 * k);
+                if (tile + 4 * (k + NB) < n) load(a[k], tile + 4 * (k + NB));
+            }
+    }
+}
+
+// ------------------------------------------ one member, FP16 or FP64 basis
+// A single field does not fill the matrix cores (2 of 16 columns).  With an
+// FP16 basis (half the bytes) or in FP64 one thread per 16-byte chunk of the
+// basis is faster there: 16^3x32, nvec 24, both directions, FP16 65 us against
+// 85, FP64 230 against 248.  (With a complex64 basis 116 against 114: one form
+// for every number of members.)  BT: the stored entry, cpx<double> or a 32-bit
+// FP16 pair.
+template <typename R> __device__ __forceinline__ cpx<R> bval(const cpx<R>& b) { return b; }
+template <typename R> __device__ __forceinline__ cpx<R> bval(const uint32_t& w) { return dec_pair<FMT_H16>(w); }
 
 // CPC consecutive basis entries, read once per application: non-temporal
 // loads, so the basis stream does not push the fine vector being restricted
-// out of the caches (restriction 52.6 -> 51.1 us on 16^3x32, Nvec 24; the
-// prolongation, which reads the small coarse vector, was slower with them,
-// 61.2 -> 62.8 us, and keeps plain loads).
+// out of the caches (the prolongation, which reads the small coarse vector,
+// was slower with them and keeps plain loads).
 template <typename BT, int CPC>
 __device__ __forceinline__ void ld_basis(BT (&b)[CPC], const BT* p) {
-    constexpr int bytes = (int)sizeof(BT) * CPC;
-    if constexpr (bytes == 4) {
-        b[0] = __builtin_nontemporal_load(reinterpret_cast<const BT*>(p));
-    } else if constexpr (bytes == 8) {
-        typedef int i2 __attribute__((ext_vector_type(2)));
-        const i2 v = __builtin_nontemporal_load(reinterpret_cast<const i2*>(p));
-        __builtin_memcpy(b, &v, 8);
+    constexpr int words = (int)sizeof(BT) * CPC / 4;
+    if constexpr (words == 1) {
+        const int v = __builtin_nontemporal_load(reinterpret_cast<const int*>(p));
+        __builtin_memcpy(b, &v, 4);
     } else {
-        static_assert(bytes % 16 == 0, "basis chunks of 4, 8 or a multiple of 16 bytes");
-        typedef int i4 __attribute__((ext_vector_type(4)));
-        i4 v[bytes / 16];
-#pragma unroll
-        for (int i = 0; i < bytes / 16; ++i) v[i] = __builtin_nontemporal_load(reinterpret_cast<const i4*>(p) + i);
-        __builtin_memcpy(b, v, bytes);
+        typedef int vec __attribute__((ext_vector_type(words)));
+        static_assert(words == 2 || words == 4, "basis chunks of 4, 8 or 16 bytes");
+        const vec v = __builtin_nontemporal_load(reinterpret_cast<const vec*>(p));
+        __builtin_memcpy(b, &v, sizeof(v));
     }
 }
 
@@ -171,13 +527,11 @@ __device__ __forceinline__ void ld_basis(BT (&b)[CPC], const BT* p) {
 // HBM latency.  The `cpr` chunks of a row (x, f) are then summed in LDS in a
 // fixed order, one thread per row.
 template <typename R, typename BT, int CPC, int RPT>
-__global__ __launch_bounds__(256) void k_prolong(cpx<R>* __restrict__ out, const BT* __restrict__ B,
+__global__ __launch_bounds__(256) void k_prolong_one(cpx<R>* __restrict__ out, const BT* __restrict__ B,
                                                  const cpx<R>* __restrict__ uc, const int* __restrict__ owner,
-                                                 int64_t V, int dof, int nvec, int rows_per_wg, int64_t cstride) {
+                                                 int64_t V, int dof, int nvec, int rows_per_wg) {
     constexpr int cpc = CPC;
     __shared__ cpx<R> part[RPT][256];
-    out += (int64_t)blockIdx.y * V * dof;          // batch member
-    uc += (int64_t)blockIdx.y * cstride;
     const int cpr = nvec / cpc;                    // chunks per row
     const int t = threadIdx.x;
     const int lr = t / cpr, kc = t - (t / cpr) * cpr;
@@ -231,13 +585,11 @@ __global__ __launch_bounds__(256) void k_prolong(cpx<R>* __restrict__ out, const
 // order.  No atomics; bitwise repeatable.  With S = 1 the threads stride over
 // the chunks instead (blocks with more chunks than threads).
 template <typename R, typename BT, int CPC>
-__global__ __launch_bounds__(1024) void k_restrict(cpx<R>* __restrict__ out, const BT* __restrict__ B,
+__global__ __launch_bounds__(1024) void k_restrict_one(cpx<R>* __restrict__ out, const BT* __restrict__ B,
                                                    const cpx<R>* __restrict__ in, const int* __restrict__ members,
-                                                   int dof, int nvec, int bsites, int64_t fstride, int S) {
+                                                   int dof, int nvec, int bsites, int S) {
     constexpr int cpc = CPC;
     extern __shared__ __align__(16) unsigned char smem[];
-    in += (int64_t)blockIdx.y * fstride;           // batch member
-    out += (int64_t)blockIdx.y * gridDim.x * 2 * nvec;
     cpx<R>* acc_l = reinterpret_cast<cpx<R>*>(smem);   // [S][dof][nvec]
     const int64_t xc = blockIdx.x;
     const int* mem = members + xc * bsites;
@@ -490,22 +842,94 @@ extern "C" qmg_status qmg_transfer_export(qmg_transfer t, void* basis, void* str
 }
 
 namespace qmg {
-template <typename R, typename BT, int CPC>
+template <typename R, typename ST, int KS, int NT>
+static void prolong_nt(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+    const int tiles = (t->bsites * (t->dof / 2) + 15) / 16;
+    // work-groups per (aggregate, chirality): at most kProlongTiles tiles each,
+    // fewer (but one per wave) where that leaves the chip without 2048 of them
+    int64_t slabs = (tiles + kProlongTiles<R> - 1) / kProlongTiles<R>;
+    const int64_t fill = (2048 + 2 * t->Vc - 1) / (2 * t->Vc);
+    if (slabs < fill) slabs = fill < (tiles + 3) / 4 ? fill : (tiles + 3) / 4;
+    const dim3 grid((unsigned)agg_grid(t->Vc), (unsigned)((nb + 8 * NT - 1) / (8 * NT)), (unsigned)slabs);
+    // the rows of a pair share a site, and pairs start at even components
+    const int wide = (t->dof / 2) % 2 == 0 && (uintptr_t)out % 16 == 0;
+    if (2 * t->nvec == 4 * KS)
+        hipLaunchKernelGGL((k_prolong<R, ST, KS, NT, true>), grid, dim3(256), 0, s, (cpx<R>*)out, (const ST*)B,
+                           (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, t->V, t->Vc, nb, wide);
+    else
+        hipLaunchKernelGGL((k_prolong<R, ST, KS, NT, false>), grid, dim3(256), 0, s, (cpx<R>*)out, (const ST*)B,
+                           (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, t->V, t->Vc, nb, wide);
+}
+
+template <typename R, typename ST, int KS>
+static void prolong_ks(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+    // column tiles per wave: the coarse operand takes KS x NT registers
+    if (nb <= 8) return prolong_nt<R, ST, KS, 1>(t, B, in, out, nb, s);
+    if constexpr (KS * sizeof(R) <= 64)
+        if (nb > 16) return prolong_nt<R, ST, KS, 4>(t, B, in, out, nb, s);
+    prolong_nt<R, ST, KS, 2>(t, B, in, out, nb, s);
+}
+
+template <typename R, typename ST>
 static qmg_status prolong_t(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+    const int nv = t->nvec;
+    if (nv <= 8) prolong_ks<R, ST, 4>(t, B, in, out, nb, s);
+    else if (nv <= 16) prolong_ks<R, ST, 8>(t, B, in, out, nb, s);
+    else if (nv <= 24) prolong_ks<R, ST, 12>(t, B, in, out, nb, s);
+    else if (nv <= 32) prolong_ks<R, ST, 16>(t, B, in, out, nb, s);
+    else prolong_ks<R, ST, 32>(t, B, in, out, nb, s);
+    QMG_LAUNCH_CHECK();
+    return QMG_OK;
+}
+
+template <typename R, typename ST, int T, int NT>
+static void restrict_nt(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+    // the split of the rows is not a function of the number of members, which keep one order of summation
+    const size_t lds = sizeof(R) * kRestrictWaves * 16 * std::max(restrict_ld(NT), 16 * T);
+    const dim3 grid((unsigned)agg_grid(t->Vc), (unsigned)((nb + 8 * NT - 1) / (8 * NT)), (unsigned)((t->nvec + 31) / 32));
+    if (t->nvec == 8 * T)
+        hipLaunchKernelGGL((k_restrict<R, ST, T, NT, true>), grid, dim3(64 * kRestrictWaves), lds, s, (cpx<R>*)out,
+                           (const ST*)B, (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, t->V, t->Vc, nb);
+    else
+        hipLaunchKernelGGL((k_restrict<R, ST, T, NT, false>), grid, dim3(64 * kRestrictWaves), lds, s, (cpx<R>*)out,
+                           (const ST*)B, (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, t->V, t->Vc, nb);
+}
+
+template <typename R, typename ST, int T>
+static void restrict_tt(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+    if (nb <= 8) return restrict_nt<R, ST, T, 1>(t, B, in, out, nb, s);
+    if constexpr (sizeof(R) == 4)
+        if (nb > 16) return restrict_nt<R, ST, T, 4>(t, B, in, out, nb, s);
+    restrict_nt<R, ST, T, 2>(t, B, in, out, nb, s);
+}
+
+template <typename R, typename ST>
+static qmg_status restrict_t(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+    const int nv = t->nvec;
+    if (nv <= 8) restrict_tt<R, ST, 1>(t, B, in, out, nb, s);
+    else if (nv <= 16) restrict_tt<R, ST, 2>(t, B, in, out, nb, s);
+    else if (nv <= 24) restrict_tt<R, ST, 3>(t, B, in, out, nb, s);
+    else restrict_tt<R, ST, 4>(t, B, in, out, nb, s);
+    QMG_LAUNCH_CHECK();
+    return QMG_OK;
+}
+
+template <typename R, typename BT, int CPC>
+static qmg_status prolong_one(qmg_transfer t, const void* B, const void* in, void* out, hipStream_t s) {
     constexpr int RPT = 4;
     const int cpr = t->nvec / CPC;
     const int rows_per_wg = 256 / cpr;
     const int64_t rows = t->V * t->dof;
     const int64_t per_wg = (int64_t)rows_per_wg * RPT;
     const unsigned nblk = (unsigned)((rows + per_wg - 1) / per_wg);
-    hipLaunchKernelGGL((k_prolong<R, BT, CPC, RPT>), dim3(nblk, nb), dim3(256), 0, s, (cpx<R>*)out, (const BT*)B,
-                       (const cpx<R>*)in, t->owner, t->V, t->dof, t->nvec, rows_per_wg, t->Vc * 2 * t->nvec);
+    hipLaunchKernelGGL((k_prolong_one<R, BT, CPC, RPT>), dim3(nblk), dim3(256), 0, s, (cpx<R>*)out, (const BT*)B,
+                       (const cpx<R>*)in, t->owner, t->V, t->dof, t->nvec, rows_per_wg);
     QMG_LAUNCH_CHECK();
     return QMG_OK;
 }
 
 template <typename R, typename BT, int CPC>
-static qmg_status restrict_t(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+static qmg_status restrict_one(qmg_transfer t, const void* B, const void* in, void* out, hipStream_t s) {
     const int nchunk = t->dof * (t->nvec / CPC);
     const size_t lds1 = sizeof(cpx<R>) * t->dof * t->nvec;
     // site slices per aggregate: as many as fit in 1024 threads and 64 KiB of
@@ -520,38 +944,40 @@ static qmg_status restrict_t(qmg_transfer t, const void* B, const void* in, void
     if (threads > 1024) threads = 1024;
     const size_t lds = lds1 * S;
     if (lds > 65536)
-        QMG_HIP(hipFuncSetAttribute((const void*)k_restrict<R, BT, CPC>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        QMG_HIP(hipFuncSetAttribute((const void*)k_restrict_one<R, BT, CPC>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)lds));
-    hipLaunchKernelGGL((k_restrict<R, BT, CPC>), dim3((unsigned)t->Vc, nb), dim3(threads), lds, s, (cpx<R>*)out,
-                       (const BT*)B, (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, t->V * t->dof, S);
+    hipLaunchKernelGGL((k_restrict_one<R, BT, CPC>), dim3((unsigned)t->Vc), dim3(threads), lds, s, (cpx<R>*)out,
+                       (const BT*)B, (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, S);
     QMG_LAUNCH_CHECK();
     return QMG_OK;
 }
 
-// complex64 fields with a 16-bit basis: 16-byte chunks of four FP16 pairs
-// where nvec allows, else 8 or 4 bytes
+// one member in FP64 or with an FP16 basis (16-byte chunks of four pairs where
+// nvec allows, else 8 or 4 bytes); every other call goes to the dense products
+static bool one_member(qmg_transfer t, qmg_prec p, int nb) { return nb == 1 && (p == QMG_C128 || t->storage == QMG_H16); }
+
 qmg_status transfer_prolong(qmg_transfer t, const void* in, void* out, qmg_prec p, int nb, hipStream_t s) {
-    using C64 = cpx<float>;
-    if (p == QMG_C128) return prolong_t<double, cpx<double>, 1>(t, t->basis64, in, out, nb, s);
-    if (t->storage == QMG_H16) {
-        if (t->nvec % 4 == 0) return prolong_t<float, uint32_t, 4>(t, t->basis, in, out, nb, s);
-        if (t->nvec % 2 == 0) return prolong_t<float, uint32_t, 2>(t, t->basis, in, out, nb, s);
-        return prolong_t<float, uint32_t, 1>(t, t->basis, in, out, nb, s);
+    if (one_member(t, p, nb)) {
+        if (p == QMG_C128) return prolong_one<double, cpx<double>, 1>(t, t->basis64, in, out, s);
+        if (t->nvec % 4 == 0) return prolong_one<float, uint32_t, 4>(t, t->basis, in, out, s);
+        if (t->nvec % 2 == 0) return prolong_one<float, uint32_t, 2>(t, t->basis, in, out, s);
+        return prolong_one<float, uint32_t, 1>(t, t->basis, in, out, s);
     }
-    if (t->nvec % 2) return prolong_t<float, C64, 1>(t, t->basis, in, out, nb, s);
-    return prolong_t<float, C64, 2>(t, t->basis, in, out, nb, s);
+    if (p == QMG_C128) return prolong_t<double, double>(t, t->basis64, in, out, nb, s);
+    if (t->storage == QMG_H16) return prolong_t<float, _Float16>(t, t->basis, in, out, nb, s);
+    return prolong_t<float, float>(t, t->basis, in, out, nb, s);
 }
 
 qmg_status transfer_restrict(qmg_transfer t, const void* in, void* out, qmg_prec p, int nb, hipStream_t s) {
-    using C64 = cpx<float>;
-    if (p == QMG_C128) return restrict_t<double, cpx<double>, 1>(t, t->basis64, in, out, nb, s);
-    if (t->storage == QMG_H16) {
-        if (t->nvec % 4 == 0) return restrict_t<float, uint32_t, 4>(t, t->basis, in, out, nb, s);
-        if (t->nvec % 2 == 0) return restrict_t<float, uint32_t, 2>(t, t->basis, in, out, nb, s);
-        return restrict_t<float, uint32_t, 1>(t, t->basis, in, out, nb, s);
+    if (one_member(t, p, nb)) {
+        if (p == QMG_C128) return restrict_one<double, cpx<double>, 1>(t, t->basis64, in, out, s);
+        if (t->nvec % 4 == 0) return restrict_one<float, uint32_t, 4>(t, t->basis, in, out, s);
+        if (t->nvec % 2 == 0) return restrict_one<float, uint32_t, 2>(t, t->basis, in, out, s);
+        return restrict_one<float, uint32_t, 1>(t, t->basis, in, out, s);
     }
-    if (t->nvec % 2) return restrict_t<float, C64, 1>(t, t->basis, in, out, nb, s);
-    return restrict_t<float, C64, 2>(t, t->basis, in, out, nb, s);
+    if (p == QMG_C128) return restrict_t<double, double>(t, t->basis64, in, out, nb, s);
+    if (t->storage == QMG_H16) return restrict_t<float, _Float16>(t, t->basis, in, out, nb, s);
+    return restrict_t<float, float>(t, t->basis, in, out, nb, s);
 }
 }  // namespace qmg
 

@@ -101,3 +101,41 @@ def test_fp16_basis_prolong_restrict(dims, dof, block, nvec):
     print(dims, dof, block, nvec, 'fp16 basis: arithmetic %.1e %.1e, storage %.1e %.1e' % (e_pq, e_rq, e_p, e_r))
     # complex128 fields use the FP64 basis whatever the storage
     assert rel_err(host(t.prolong(dev(uc))), transfer.prolong(Vb, uc, dims, block)) <= 1e-12
+
+
+@pytest.mark.parametrize('storage', ['c64', 'c128', 'h16'])
+@pytest.mark.parametrize('dims,dof,block,nvec,nrhs', [
+    ((4, 6, 2, 4), 12, (2, 3, 1, 2), 1, 9),        # one vector; a second column tile with one member
+    ((4, 4, 4, 6), 12, (2, 2, 2, 3), 24, 17),      # whole column tiles, a third one; rows end inside a tile
+    ((6, 6, 2, 2), 6, (3, 3, 1, 1), 13, 8),        # three rows per site and chirality: pairs of rows straddle sites
+    ((4, 4, 4, 4), 12, (2, 2, 2, 2), 33, 33),      # a second block of vectors, a second group of members
+    ((2, 4, 2, 2), 46, (1, 2, 1, 1), 32, 2),       # fewer rows than waves take
+])
+def test_batched_transfers_at_the_edges_of_the_tiles(dims, dof, block, nvec, nrhs, storage):
+    """Batches through the dense products at the remainders of rows, vectors and
+    members, into fields that are only element-aligned: each member against the
+    oracle (FP32 sums of at most a few hundred products: 1e-5; FP64 1e-12), and with
+    complex64 storage (one form for every number of members) bitwise against its
+    single call."""
+    from paper_1612_07873_amd import Transfer
+    V = lattice.volume(dims)
+    vecs = synth.gaussian((nvec, V, dof), 11, 1)
+    Vb = transfer.block_orthonormalize(vecs, dims, block)
+    Vc = lattice.volume(transfer.coarse_dims(dims, block))
+    UC = np.stack([synth.gaussian((Vc, 2 * nvec), 60 + k, 2) for k in range(nrhs)])
+    F = np.stack([synth.gaussian((V, dof), 160 + k, 2) for k in range(nrhs)])
+    cdt = torch.complex128 if storage == 'c128' else torch.complex64
+    t = Transfer(dims, dof, block, dev(vecs), storage)
+    off = lambda shape: torch.full((int(np.prod(shape)) + 1,), float('nan'), dtype=cdt, device='cuda')[1:].view(shape)
+    p, r = off((nrhs, V, dof)), off((nrhs, Vc, 2 * nvec))
+    t.prolong(dev(UC, cdt), p)
+    t.restrict(dev(F, cdt), r)
+    Vr = _fp16_basis(Vb) if storage == 'h16' else Vb
+    tol = 1e-12 if storage == 'c128' else 1e-5
+    ep = max(rel_err(host(p)[k], transfer.prolong(Vr, UC[k], dims, block)) for k in range(nrhs))
+    er = max(rel_err(host(r)[k], transfer.restrict(Vr, F[k], dims, block)) for k in range(nrhs))
+    print(dims, dof, block, nvec, nrhs, storage, 'prolong %.1e restrict %.1e' % (ep, er))
+    assert ep <= tol and er <= tol, (ep, er)
+    if storage == 'c64':
+        k = nrhs - 1
+        assert torch.equal(t.prolong(dev(UC[k], cdt)), p[k]) and torch.equal(t.restrict(dev(F[k], cdt)), r[k])
