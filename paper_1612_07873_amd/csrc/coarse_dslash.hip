@@ -38,6 +38,7 @@
 #include "handles.h"
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 namespace qmg {
@@ -297,6 +298,175 @@ __global__ __launch_bounds__(1024) void k_coarse_dslash(const typename Fmt<F>::C
     }
 }
 
+// Several right-hand sides (vectors in the accumulation precision).  The
+// stencil above launched once per member re-reads the links for each (4^3x8,
+// N = 64, complex64, twelve members: 125 us per red-black piece, whose links are
+// 67 MB; this kernel takes 30).  Here a work-group applies its link chunks to MB members, and a
+// thread to RR rows, so that a chunk and a staged input pair are each used
+// RR * MB times; the bound is then the FP32 multiply-adds and the LDS reads
+// that feed them (16 multiply-adds per 16-byte read at RR = 2).  Every
+// (row, split lane, member) sums the same products in the same order as the
+// single-member stencil with the same launch, so a member of a batch equals
+// the single call bitwise: chunk k goes to accumulator k mod 4, except that
+// with `pre` = 1 the count starts at the second chunk, and that the chunks
+// after the last whole group of four all go to accumulator 0 unless there are
+// fewer than `pre` in all.  The chunks are loaded one group ahead, in pairs, so
+// that two work-groups of 512 threads fit the registers of a CU.
+// The G = ceil(m / MB) work-groups of a (site, row tile) run next to each other
+// on one XCD, whose L2 then serves the links to all but the first.
+template <int F, int RR, int MB, bool EO>
+__global__ __launch_bounds__(1024 / RR, F == FMT_F64 ? 2 : 4) void k_coarse_batch(const typename Fmt<F>::C* __restrict__ L,
+                                                            const float* __restrict__ lscale,
+                                                            const int* __restrict__ nbr, const void* __restrict__ uin,
+                                                            void* __restrict__ yout, int N, int J, int rows, int split,
+                                                            int pre, int ntiles, int64_t V, int m, int G, EoArgs ea) {
+    using R = typename Fmt<F>::R;
+    using C = typename Fmt<F>::C;
+    constexpr int cpc = Fmt<F>::cpc;
+    extern __shared__ __align__(16) unsigned char smem[];
+    cpx<R>* ul = reinterpret_cast<cpx<R>*>(smem);   // [MB][9N] stacked inputs, then [MB][split][rows] partial sums
+    const int64_t i = blockIdx.x >> 3;
+    const int64_t unit = (i / G) * 8 + (blockIdx.x & 7);
+    if (unit >= V * ntiles) return;   // the whole work-group
+    const int j0 = (int)(i % G) * MB;
+    const int mm = m - j0 < MB ? m - j0 : MB;
+    const int site = (int)(unit / ntiles);
+    const int tile = (int)(unit - (int64_t)site * ntiles);
+    const int t = threadIdx.x;
+    const int prows = rows / RR;
+    const int T = prows * split;
+    const int rl = t % prows;
+    const int s = t / prows;
+    const int d0 = EO ? ea.d0 : 0;
+    const int nd = EO ? ea.nd : 9;
+    const int K = (EO ? nd * N / cpc : J) / split;
+    const C* Ls = L + ((int64_t)site * J + (EO ? d0 * N / cpc : 0)) * N + tile * rows + rl;
+    const int first = pre == 1 ? 1 : 0;            // chunks before the groups of four
+    const int ng = (K - first + 3) >> 2;           // groups, the last one possibly partial
+    const int part = (K - first) & 3;              // chunks of a partial last group (0: whole)
+    const bool tail0 = K >= pre;                   // a partial group goes to accumulator 0
+
+    // chunks 2 h and 2 h + 1 of group g (past the last chunk that one again, unused)
+    auto load = [&](C (&a)[2][RR], int g, int h) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            int k = first + 4 * g + 2 * h + q;
+            if (k >= K) k = K - 1;
+#pragma unroll
+            for (int p = 0; p < RR; ++p) a[q][p] = ld_link(Ls + (int64_t)(s + split * k) * N + p * prows);
+        }
+    };
+    C a[2][RR], b[2][RR];
+    if (ng > 0) {
+        load(a, 0, 0);
+        load(b, 0, 1);
+    }
+
+    for (int idx = t; idx < nd * N; idx += T) {
+        const int dd = idx / N;
+        const int d = dd + d0;
+        const int c = idx - dd * N;
+        const cpx<R>* src;
+        int64_t step;                              // member stride
+        if constexpr (EO) {
+            const bool loc = d == 0;
+            src = reinterpret_cast<const cpx<R>*>(loc ? ea.uself : uin) +
+                  (int64_t)(loc ? (ea.sidx ? ea.sidx[site] : site) : nbr[site * 8 + d - 1]) * N + c;
+            step = (loc ? ea.vself : V) * N;
+        } else {
+            src = reinterpret_cast<const cpx<R>*>(uin) + (int64_t)(d == 0 ? site : nbr[site * 8 + d - 1]) * N + c;
+            step = V * N;
+        }
+        float sl = 1.0f;
+        if constexpr (F == FMT_H16 || F == FMT_B16) sl = lscale[site * 9 + d];
+        cpx<R> v[MB];
+#pragma unroll
+        for (int j = 0; j < MB; ++j) v[j] = src[(int64_t)(j0 + (j < mm ? j : mm - 1)) * step];
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            if constexpr (F == FMT_H16 || F == FMT_B16) {
+                v[j].re *= sl;
+                v[j].im *= sl;
+            }
+            ul[j * 9 * N + idx] = v[j];
+        }
+    }
+    __syncthreads();
+
+    R ar[MB][RR][4], ai[MB][RR][4];
+#pragma unroll
+    for (int j = 0; j < MB; ++j)
+#pragma unroll
+        for (int p = 0; p < RR; ++p)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) ar[j][p][q] = ai[j][p][q] = 0;
+    auto chunk = [&](const C (&c)[RR], int k, auto acc) {   // chunk k to accumulator `acc`
+        constexpr int q = decltype(acc)::value;
+        const cpx<R>* u = ul + (s + split * k) * cpc;
+#pragma unroll
+        for (int j = 0; j < MB; ++j)
+#pragma unroll
+            for (int p = 0; p < RR; ++p) mac<F>(c[p], u + j * 9 * N, ar[j][p][q], ai[j][p][q]);
+    };
+    using A0 = std::integral_constant<int, 0>;
+    using A1 = std::integral_constant<int, 1>;
+    using A2 = std::integral_constant<int, 2>;
+    using A3 = std::integral_constant<int, 3>;
+    if (first) {
+        C h[RR];
+#pragma unroll
+        for (int p = 0; p < RR; ++p) h[p] = ld_link(Ls + (int64_t)s * N + p * prows);
+        chunk(h, 0, A0{});
+    }
+    // all groups but the last: their loads are unconditional (a load under a
+    // condition makes the next wait one for all loads before it)
+    int k = first;
+    for (int g = 0; g + 1 < ng; ++g, k += 4) {
+        chunk(a[0], k, A0{});
+        chunk(a[1], k + 1, A1{});
+        load(a, g + 1, 0);
+        chunk(b[0], k + 2, A2{});
+        chunk(b[1], k + 3, A3{});
+        load(b, g + 1, 1);
+    }
+    if (ng > 0) {
+        chunk(a[0], k, A0{});
+        if (part == 0) {
+            chunk(a[1], k + 1, A1{});
+            chunk(b[0], k + 2, A2{});
+            chunk(b[1], k + 3, A3{});
+        } else if (tail0) {
+            if (part > 1) chunk(a[1], k + 1, A0{});
+            if (part > 2) chunk(b[0], k + 2, A0{});
+        } else {
+            if (part > 1) chunk(a[1], k + 1, A1{});
+            if (part > 2) chunk(b[0], k + 2, A2{});
+        }
+    }
+    __syncthreads();   // every read of the inputs is done
+#pragma unroll
+    for (int j = 0; j < MB; ++j)
+#pragma unroll
+        for (int p = 0; p < RR; ++p) {
+            const R sr = (ar[j][p][0] + ar[j][p][1]) + (ar[j][p][2] + ar[j][p][3]);
+            const R si = (ai[j][p][0] + ai[j][p][1]) + (ai[j][p][2] + ai[j][p][3]);
+            ul[(j * split + s) * rows + rl + p * prows] = cpx<R>{sr, si};
+        }
+    __syncthreads();
+    const int64_t o = EO && ea.oidx ? ea.oidx[site] : site;
+    const int64_t os = EO ? ea.vout : V;
+    for (int e = t; e < mm * rows; e += T) {
+        const int j = e / rows, r = e - j * rows;
+        const cpx<R>* p = ul + j * split * rows + r;
+        R sr = p[0].re, si = p[0].im;
+        for (int q = 1; q < split; ++q) {
+            sr += p[q * rows].re;
+            si += p[q * rows].im;
+        }
+        reinterpret_cast<cpx<R>*>(yout)[(o + (j0 + j) * os) * N + tile * rows + r] = cpx<R>{sr, si};
+    }
+}
+
 // -------------------------------------------------------- vector (de)quantise
 template <int VF>
 __global__ __launch_bounds__(64) void k_quantize(const float2* __restrict__ in, uint32_t* __restrict__ out,
@@ -397,6 +567,61 @@ static qmg_status validate_launch(const qmg_coarse_op_s* op, int rows, int split
     return QMG_OK;
 }
 
+// Members per work-group of the batched stencil, the groups as even as
+// possible: up to three, four in FP64 (a fourth in FP32 spills at the 128
+// registers that let two work-groups share a CU: 4^3x8 N = 64 red-black, twelve
+// members, complex64, 82 us with four, 60 with three).
+template <int F> static int batch_members(int m) {
+    constexpr int most = F == FMT_F64 ? 4 : 3;
+    const int G = (m + most - 1) / most;
+    return (m + G - 1) / G;
+}
+// Whether m > 1 members take the batched stencil: not where it has fewer than
+// 100 work-groups, each of which then reads its links for all its members in
+// one long latency chain that the work-groups of one member each run side by
+// side (red-black N = 64, complex64, twelve members, batched against per
+// member: 64 work-groups 15.5 against 12.2 us, 128 18.8 against 27.0 us).
+template <int F> static bool use_batch(const qmg_coarse_op_s* op, int rows, int m) {
+    if (m < 2) return false;
+    const int mb = batch_members<F>(m);
+    return op->V * (op->N / rows) * ((m + mb - 1) / mb) >= 100;
+}
+
+// The stencil (or a red-black piece of it) for several members with the launch
+// shape of a single one: two rows per thread where a work-group's rows pair up.
+template <int F, int RR, int MB, bool EO>
+static qmg_status launch_batch_t(const qmg_coarse_op_s* op, int rows, int split, int pre, const EoArgs& ea,
+                                 const void* in, void* out, int m, hipStream_t s) {
+    using R = typename Fmt<F>::R;
+    const int ntiles = op->N / rows, G = (m + MB - 1) / MB;
+    const size_t lds = sizeof(cpx<R>) * MB * std::max(9 * op->N, rows * split);
+    auto kern = k_coarse_batch<F, RR, MB, EO>;
+    if (lds > 65536) QMG_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const dim3 grid((unsigned)((op->V * ntiles + 7) / 8 * 8 * G)), block((unsigned)(rows / RR * split));
+    hipLaunchKernelGGL(kern, grid, block, lds, s, reinterpret_cast<const typename Fmt<F>::C*>(op->links), op->lscale,
+                       op->nbr, in, out, op->N, op->J, rows, split, pre, ntiles, op->V, m, G, ea);
+    QMG_LAUNCH_CHECK();
+    return QMG_OK;
+}
+
+template <int F, bool EO>
+static qmg_status launch_batch(const qmg_coarse_op_s* op, int rows, int split, int pre, const EoArgs& ea,
+                               const void* in, void* out, int m, hipStream_t s) {
+    const int mb = batch_members<F>(m);
+    if (rows % 2) {
+        if (mb == 2) return launch_batch_t<F, 1, 2, EO>(op, rows, split, pre, ea, in, out, m, s);
+        if (mb == 3) return launch_batch_t<F, 1, 3, EO>(op, rows, split, pre, ea, in, out, m, s);
+    } else {
+        if (mb == 2) return launch_batch_t<F, 2, 2, EO>(op, rows, split, pre, ea, in, out, m, s);
+        if (mb == 3) return launch_batch_t<F, 2, 3, EO>(op, rows, split, pre, ea, in, out, m, s);
+    }
+    if constexpr (F == FMT_F64) {
+        if (rows % 2) return launch_batch_t<F, 1, 4, EO>(op, rows, split, pre, ea, in, out, m, s);
+        return launch_batch_t<F, 2, 4, EO>(op, rows, split, pre, ea, in, out, m, s);
+    }
+    return fail(QMG_ERR_ARG, "coarse stencil: %d members", m);
+}
+
 template <int F, int VF>
 static qmg_status launch_f(const qmg_coarse_op_s* op, int rows, int split, int pre, const void* in,
                            const float* in_scale, void* out, float* out_scale, int m, hipStream_t s) {
@@ -407,12 +632,15 @@ static qmg_status launch_f(const qmg_coarse_op_s* op, int rows, int split, int p
     const auto* L = reinterpret_cast<const typename Fmt<F>::C*>(op->links);
     const int K = op->J / split;
     if (pre <= 0) pre = K >= 16 ? 16 : 4;
+    pre = pre >= 16 ? 16 : pre >= 8 ? 8 : pre >= 4 ? 4 : 1;
+    if constexpr (VF == 0)
+        if (use_batch<F>(op, rows, m)) return launch_batch<F, false>(op, rows, split, pre, EoArgs{}, in, out, m, s);
 #define QMG_CD_LAUNCH(P)                                                                                          \
     hipLaunchKernelGGL((k_coarse_dslash<F, VF, P>), grid, block, lds, s, L, op->lscale, op->nbr, in, in_scale, out, \
                        out_scale, op->N, op->J, rows, split, ntiles, op->V, EoArgs{})
-    if (pre >= 16) QMG_CD_LAUNCH(16);
-    else if (pre >= 8) QMG_CD_LAUNCH(8);
-    else if (pre >= 4) QMG_CD_LAUNCH(4);
+    if (pre == 16) QMG_CD_LAUNCH(16);
+    else if (pre == 8) QMG_CD_LAUNCH(8);
+    else if (pre == 4) QMG_CD_LAUNCH(4);
     else QMG_CD_LAUNCH(1);
 #undef QMG_CD_LAUNCH
     QMG_LAUNCH_CHECK();
@@ -477,6 +705,7 @@ static qmg_status launch_eo_f(const qmg_coarse_op_s* op, const EoArgs& ea, const
     const dim3 grid((unsigned)(op->V * ntiles), (unsigned)m), block((unsigned)(rows * split));
     const auto* L = reinterpret_cast<const typename Fmt<F>::C*>(op->links);
     const int K = ea.nd * op->N / Fmt<F>::cpc / split;
+    if (use_batch<F>(op, rows, m)) return launch_batch<F, true>(op, rows, split, K >= 16 ? 16 : 4, ea, in, out, m, s);
     if (K >= 16)
         hipLaunchKernelGGL((k_coarse_dslash<F, 0, 16, true>), grid, block, lds, s, L, op->lscale, op->nbr, in, nullptr,
                            out, nullptr, op->N, op->J, rows, split, ntiles, op->V, ea);

@@ -122,3 +122,41 @@ def test_interface_errors(galerkin_8x8x8x8_op):
         g.set_launch(48, 432)       # more than 1024 threads
     g.set_launch(0, 0)
     assert g.launch()[0] > 0
+
+
+@pytest.mark.parametrize('storage', ['c128', 'c64', 'h16'])
+@pytest.mark.parametrize('cdims,N,nrhs,launches', [
+    # (rows, split): two rows per thread or one (odd row tiles), 1 to 3 chunks
+    # left after the groups of four, fewer chunks than a group
+    ((5, 2, 4, 5), 12, 2, [(12, 1), (3, 9), (6, 3), (12, 27)]),
+    ((4, 4, 4, 4), 20, 7, [(20, 1), (5, 5), (10, 9), (20, 45)]),
+    ((2, 4, 6, 4), 48, 9, [(48, 1), (16, 9), (48, 12), (24, 36), (3, 108)]),
+])
+def test_batched_stencil_equals_the_single_one(cdims, N, nrhs, launches, storage):
+    """The batched stencil sums in the single one's order whatever the launch
+    shape: every member bitwise equal to its single call, whole lattice and (all
+    extents even) red-black, and the single call against the oracle."""
+    from paper_1612_07873_amd import CoarseOp
+    op = random_op(cdims, N, 40)
+    V = lattice.volume(cdims)
+    U = np.stack([synth.gaussian((V, N), 70 + k, 2) for k in range(nrhs)])
+    dt = torch.complex128 if storage == 'c128' else torch.complex64
+    g = CoarseOp(op.dims, dev(op.X), dev(op.Y), storage)
+    ud = dev(U, dt)
+    ref = op.apply(U[0])
+    n = 0
+    for rows, split in launches:
+        if g.chunks_per_row // (2 if storage == 'h16' else 1) % split:
+            continue
+        g.set_launch(rows, split)
+        y = g.apply(ud)
+        one = [g.apply(ud[k].contiguous()) for k in range(nrhs)]
+        assert all(torch.equal(y[k], one[k]) for k in range(nrhs)), (rows, split)
+        assert rel_err(host(one[0]), ref) <= {'c128': 1e-12, 'c64': 1e-5, 'h16': 5e-3}[storage]
+        n += 1
+    assert n >= 2
+    if all(d % 2 == 0 for d in cdims):
+        g.prepare_schur()
+        ue = ud[:, :V // 2].contiguous()
+        y = g.schur(ue)
+        assert all(torch.equal(y[k], g.schur(ue[k].contiguous())) for k in range(nrhs))
