@@ -44,8 +44,8 @@ __device__ __forceinline__ void herm_mul(cpx<float> out[12], const cpx<float> x[
             for (int r = 0; r < 6; ++r)
 #pragma unroll
                 for (int c = r + 1; c < 6; ++c, ++k) {
-                    if (r == i) t = cadd(t, cmul(o[chi][k], v[c]));
-                    if (c == i) t = cadd(t, cmulc(o[chi][k], v[r]));
+                    if (r == i) t = cfma(t, o[chi][k], v[c]);
+                    if (c == i) t = cfmac(t, o[chi][k], v[r]);
                 }
             out[6 * chi + i] = t;
         }

@@ -28,7 +28,9 @@
 // (the largest |re| or |im| of its 12 components).
 #include "wilson_dev.h"
 
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 namespace qmg {
@@ -191,7 +193,7 @@ __global__ __launch_bounds__(256) void k_wilson_clover(const void* __restrict__ 
 #pragma unroll
             for (int f = 0; f < 12; ++f) p[f] = sh[f * kWilsonSites + t];
 #pragma unroll
-            for (int f = 0; f < 12; ++f) acc[f] = {acc[f].re + diag * p[f].re, acc[f].im + diag * p[f].im};
+            for (int f = 0; f < 12; ++f) acc[f] = {fmadd(diag, p[f].re, acc[f].re), fmadd(diag, p[f].im, acc[f].im)};
             if (use_clover) herm_mul_add<LF>(acc, p, clov, cscale, site, V);
         }
         hop_apply<1, false>(acc, pa, ua);
@@ -215,7 +217,7 @@ __global__ __launch_bounds__(256) void k_wilson_clover(const void* __restrict__ 
 #pragma unroll
         for (int f = 0; f < 12; ++f) pa[f] = sh[f * kWilsonSites + t];
 #pragma unroll
-        for (int f = 0; f < 12; ++f) acc[f] = {acc[f].re + diag * pa[f].re, acc[f].im + diag * pa[f].im};
+        for (int f = 0; f < 12; ++f) acc[f] = {fmadd(diag, pa[f].re, acc[f].re), fmadd(diag, pa[f].im, acc[f].im)};
         if (use_clover) herm_mul_add<LF>(acc, pa, clov, cscale, site, V);
         hop_load_near<NEAR, 1, false, LF, VF, LR>(pa, ua, sh, in, in_scale, U, V, site, nb[2], base, vo, last);
         hop_apply<1, false>(acc, pa, ua);
@@ -400,6 +402,235 @@ __global__ __launch_bounds__(256) void k_wilson_eo(const void* __restrict__ U, c
         store_spinor<VF>(out, sc.out, out_full ? site + vf : h + vh, t);
     } else {
         store_spinor<VF>(out, sc.out, out_full ? site + vf : h + vh, acc);
+    }
+}
+
+// ------------------------------------------- one wave per hop direction
+// The same application with the eight hops of a site taken by eight waves: a
+// work-group covers 64 sites, wave d (0..7) multiplies the projected half
+// spinor of direction d by its link and leaves the two upper spins in LDS, two
+// waves (SELF 2), one per chirality, leave the clover term's product there, and
+// two more add it all up and store.  What a wave needs of the operator -- a link, or one
+// chirality block of the clover term or of the inverse -- stays in its
+// registers while the batch's members go by, each through one of two LDS
+// buffers, one barrier per member: the links and the clover term are read once
+// for all members, and all loads of a site are in flight at once.  Twelve
+// members, complex64, 16^3x32 red-black: 179 -> 77 us per piece, 361 MB moved
+// (the members' spinors, 151 MB in and out, are fetched about three times, by
+// the work-groups one time slice apart); FP64 350 -> 176 us.  On small lattices
+// the sum's waves, one chain per member, set the time (12^3x24, FP16 links,
+// twelve members 44 -> 30 us).
+// Sums and products are those of the one-thread-per-site kernels in their
+// order (FULL lattice with whole x-y planes, ORD 1: t, z, the site-local term,
+// y, x; otherwise the site-local term, then x, y, z, t), so the two forms agree
+// bitwise and the choice between them may depend on the number of members.
+struct DirArgs {
+    const void *U, *H;          // links; clover term (SELF 2) or inverse (INV)
+    const float* hscale;
+    const int *nbr, *hsite;     // neighbour table (red-black: parity order), half-lattice sites
+    const void *self, *hin;
+    void* out;
+    int64_t Vs, V, last;        // sites of the launch, of the lattice
+    double diag, coef;
+    int self_full, out_full, parity, members, per_group, groups;
+};
+
+template <typename R> struct DirBuf;
+template <> struct DirBuf<float> {
+    using W = float4;           // two of the six complex numbers of a half spinor
+    static __device__ __forceinline__ void put(W* b, int l, const cpx<float> w[2][3]) {
+        const cpx<float>* f = &w[0][0];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) b[q * 64 + l] = make_float4(f[2 * q].re, f[2 * q].im, f[2 * q + 1].re, f[2 * q + 1].im);
+    }
+    static __device__ __forceinline__ void get(cpx<float> w[2][3], const W* b, int l) {
+        cpx<float>* f = &w[0][0];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const float4 v = b[q * 64 + l];
+            f[2 * q] = {v.x, v.y};
+            f[2 * q + 1] = {v.z, v.w};
+        }
+    }
+    static constexpr int n = 3 * 64;   // words of a direction
+};
+template <> struct DirBuf<double> {
+    using W = double2;
+    static __device__ __forceinline__ void put(W* b, int l, const cpx<double> w[2][3]) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) b[q * 64 + l] = make_double2((&w[0][0])[q].re, (&w[0][0])[q].im);
+    }
+    static __device__ __forceinline__ void get(cpx<double> w[2][3], const W* b, int l) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            const double2 v = b[q * 64 + l];
+            (&w[0][0])[q] = {v.x, v.y};
+        }
+    }
+    static constexpr int n = 6 * 64;
+};
+
+// six components of one chirality at a site
+template <typename R> __device__ __forceinline__ void load_half(cpx<R> p[6], const void* src, int64_t site, int chi) {
+    if constexpr (sizeof(R) == 4) {
+        const float4* s = static_cast<const float4*>(src) + site * 6 + 3 * chi;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const float4 v = s[i];
+            p[2 * i] = {v.x, v.y};
+            p[2 * i + 1] = {v.z, v.w};
+        }
+    } else {
+        const cpx<R>* s = static_cast<const cpx<R>*>(src) + site * 12 + 6 * chi;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) p[i] = s[i];
+    }
+}
+template <typename R> __device__ __forceinline__ void store_half(void* dst, int64_t site, int chi, const cpx<R> p[6]) {
+    if constexpr (sizeof(R) == 4) {
+        float4* d = static_cast<float4*>(dst) + site * 6 + 3 * chi;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) d[i] = make_float4(p[2 * i].re, p[2 * i].im, p[2 * i + 1].re, p[2 * i + 1].im);
+    } else {
+        cpx<R>* d = static_cast<cpx<R>*>(dst) + site * 12 + 6 * chi;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) d[i] = p[i];
+    }
+}
+
+// VF: complex64 or complex128 vectors (the arithmetic precision)
+template <int LF, int VF, int LR, bool EO, int SELF, bool INV, int ORD>
+__global__ __launch_bounds__(SELF == 2 ? 768 : 640, sizeof(typename FineT<LF>::R) == 8 ? 3 : SELF == 2 ? 6 : 5)
+    void k_wilson_dirs(DirArgs A) {
+    using R = typename FineT<LF>::R;
+    using B = DirBuf<R>;
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int slots = SELF == 2 ? 10 : 8;
+    typename B::W* buf = reinterpret_cast<typename B::W*>(smem);   // [2][slots][B::n]
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    // each XCD takes one contiguous range of site blocks, the groups of
+    // members of a block one after another (grid a multiple of 8 groups)
+    const int64_t i = blockIdx.x >> 3, per = gridDim.x / (8 * A.groups);
+    const int64_t blk = (int64_t)(blockIdx.x & 7) * per + i / A.groups;
+    const int m0 = (int)(i % A.groups) * A.per_group;
+    const int m = A.members - m0 < A.per_group ? A.members - m0 : A.per_group;
+    const bool live = blk * 64 + l < A.Vs;
+    const int64_t h = live ? blk * 64 + l : A.Vs - 1;   // lanes past the last site repeat it and store nothing
+    const int64_t ie = EO ? (int64_t)A.parity * A.Vs + h : h;
+    const int64_t site = EO ? (int64_t)A.hsite[ie] : h;
+
+    auto hops = [&](auto mu_, auto back_) {
+        constexpr int MU = decltype(mu_)::value;
+        constexpr bool BACK = decltype(back_)::value;
+        const int64_t n = A.nbr[ie * 8 + 2 * MU + BACK];
+        const int64_t sp = (EO ? n >> 1 : n) + (int64_t)m0 * A.Vs;
+        cpx<R> u[9], p[12], a[2][3], wv[2][3];
+        load_spinor<VF>(p, A.hin, nullptr, sp);
+        load_link_at<LF, LR, EO>(u, A.U, MU, BACK ? (EO ? (int64_t)(1 - A.parity) * A.Vs + (n >> 1) : n) : ie, A.V,
+                                 MU == 3 && (BACK ? n : site) >= A.last);
+        for (int j = 0; j < m; ++j) {
+            hop_project<MU, BACK>(a, p);
+            if (j + 1 < m) load_spinor<VF>(p, A.hin, nullptr, sp + (j + 1) * A.Vs);
+            hop_link<BACK>(wv, a, u);
+            B::put(buf + ((j & 1) * slots + 2 * MU + BACK) * B::n, l, wv);
+            __syncthreads();
+        }
+    };
+    const int64_t si = A.self_full ? site : h, sstep = A.self_full ? A.V : A.Vs;
+    // the clover term's product of one chirality
+    auto clover = [&](auto chi_) {
+        constexpr int CHI = decltype(chi_)::value;
+        R d[6];
+        cpx<R> o[15], p[6], t[2][3];
+        load_half(p, A.self, si + m0 * sstep, CHI);
+        load_clover<LF>(d, o, A.H, A.hscale, CHI, ie, A.V);
+        for (int j = 0; j < m; ++j) {
+            herm6_mul(&t[0][0], p, d, o);
+            if (j + 1 < m) load_half(p, A.self, si + (m0 + j + 1) * sstep, CHI);
+            B::put(buf + ((j & 1) * slots + 8 + CHI) * B::n, l, t);
+            __syncthreads();
+        }
+    };
+    // the sum of one chirality, times the inverse where asked for
+    auto total = [&](auto chi_) {
+        constexpr int CHI = decltype(chi_)::value;
+        R d[6];
+        cpx<R> o[15];
+        if constexpr (INV) load_clover<LF>(d, o, A.H, A.hscale, CHI, ie, A.V);
+        const int64_t oi = A.out_full ? site : h, ostep = A.out_full ? A.V : A.Vs;
+        const R c = R(-0.5) * (R)A.coef, diag = (R)A.diag;
+        for (int j = 0; j < m; ++j) {
+            cpx<R> p[6], acc[6], wv[2][3];
+            if constexpr (SELF != 0) load_half(p, A.self, si + (m0 + j) * sstep, CHI);
+            __syncthreads();
+            const typename B::W* b = buf + (j & 1) * slots * B::n;
+#pragma unroll
+            for (int f = 0; f < 6; ++f) acc[f] = {R(0), R(0)};
+            auto site_term = [&]() {
+                if constexpr (SELF == 1) {
+#pragma unroll
+                    for (int f = 0; f < 6; ++f) acc[f] = p[f];
+                } else if constexpr (SELF == 2) {
+                    B::get(wv, b + (8 + CHI) * B::n, l);
+#pragma unroll
+                    for (int f = 0; f < 6; ++f)
+                        acc[f] = cadd(cpx<R>{fmadd(diag, p[f].re, acc[f].re), fmadd(diag, p[f].im, acc[f].im)},
+                                      wv[f / 3][f % 3]);
+                }
+            };
+            auto add = [&](auto mu_, auto back_) {
+                constexpr int MU = decltype(mu_)::value;
+                constexpr bool BACK = decltype(back_)::value;
+                B::get(wv, b + (2 * MU + BACK) * B::n, l);
+                hop_add<MU, BACK, CHI>(acc, wv, c);
+            };
+            auto both = [&](auto mu_) {
+                add(mu_, std::false_type{});
+                add(mu_, std::true_type{});
+            };
+            using I0 = std::integral_constant<int, 0>;
+            using I1 = std::integral_constant<int, 1>;
+            using I2 = std::integral_constant<int, 2>;
+            using I3 = std::integral_constant<int, 3>;
+            if constexpr (ORD == 1) {
+                both(I3{});
+                both(I2{});
+            }
+            site_term();
+            if constexpr (ORD == 1) {
+                both(I1{});
+                both(I0{});
+            } else {
+                both(I0{});
+                both(I1{});
+                both(I2{});
+                both(I3{});
+            }
+            if constexpr (INV) {
+                cpx<R> t[6];
+                herm6_mul(t, acc, d, o);
+                if (live) store_half(A.out, oi + (m0 + j) * ostep, CHI, t);
+            } else {
+                if (live) store_half(A.out, oi + (m0 + j) * ostep, CHI, acc);
+            }
+        }
+    };
+    switch (w) {
+        case 0: hops(std::integral_constant<int, 0>{}, std::false_type{}); break;
+        case 1: hops(std::integral_constant<int, 0>{}, std::true_type{}); break;
+        case 2: hops(std::integral_constant<int, 1>{}, std::false_type{}); break;
+        case 3: hops(std::integral_constant<int, 1>{}, std::true_type{}); break;
+        case 4: hops(std::integral_constant<int, 2>{}, std::false_type{}); break;
+        case 5: hops(std::integral_constant<int, 2>{}, std::true_type{}); break;
+        case 6: hops(std::integral_constant<int, 3>{}, std::false_type{}); break;
+        case 7: hops(std::integral_constant<int, 3>{}, std::true_type{}); break;
+        case 8: total(std::integral_constant<int, 0>{}); break;
+        case 9: total(std::integral_constant<int, 1>{}); break;
+        case 10:
+            if constexpr (SELF == 2) clover(std::integral_constant<int, 0>{});
+            break;
+        default:
+            if constexpr (SELF == 2) clover(std::integral_constant<int, 1>{});
     }
 }
 
@@ -717,6 +948,35 @@ static SigmaBlocks sigma_blocks(double csw) {
 // work-groups of one member's launch (256 sites each, a multiple of 8)
 int wilson_groups(const qmg_fine_op_s* op) { return (int)(((op->V + 255) / 256 + 7) / 8 * 8); }
 
+template <int LF, int VF, int LR, bool EO, int SELF, bool INV, int ORD>
+static qmg_status launch_dirs(DirArgs A, hipStream_t s) {
+    using R = typename FineT<LF>::R;
+    const int64_t blocks = ((A.Vs + 63) / 64 + 7) / 8 * 8;
+    // all members in one work-group where the blocks alone fill the chip (two
+    // work-groups per CU); otherwise split until they do
+    A.groups = (int)std::min<int64_t>(A.members, (511 + blocks) / blocks);
+    A.per_group = (A.members + A.groups - 1) / A.groups;
+    A.groups = (A.members + A.per_group - 1) / A.per_group;
+    const size_t lds = sizeof(typename DirBuf<R>::W) * DirBuf<R>::n * (SELF == 2 ? 10 : 8) * (A.per_group > 1 ? 2 : 1);
+    auto kern = k_wilson_dirs<LF, VF, LR, EO, SELF, INV, ORD>;
+    if (lds > 65536) QMG_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(kern, dim3((unsigned)(blocks * A.groups)), dim3(SELF == 2 ? 768 : 640), lds, s, A);
+    QMG_LAUNCH_CHECK();
+    return QMG_OK;
+}
+// Which form a launch over `sites` sites takes.  Up to 32768 sites the one-thread-
+// per-site kernels leave the chip short of waves (red-black, one member: 16^3x16
+// 22.1 against 16.6 us with FP16 links, 16^3x32 31 against 38 us in FP32; whole
+// lattice FP64 7x10x9x14 17 against 8 us), and above it one member is
+// faster there.  Several members share what the direction waves hold: from two
+// on red-black (16^3x32 complex64, two members 59 against 50 us, twelve 342
+// against 148), from three on the whole lattice (two 40 against 41 us, three 59
+// against 51), where 16-bit links, half the bytes, take one more (three 48
+// against 51 us).
+static bool use_dirs(int64_t sites, int members, bool eo, bool link16) {
+    return sites <= 32768 || members >= (eo ? 2 : link16 ? 4 : 3);
+}
+
 template <int LF, int VF, bool DOT = false>
 static qmg_status launch_wilson(const qmg_fine_op_s* op, const void* in, const float* in_scale, void* out,
                                 float* out_scale, int members, hipStream_t s, double* part = nullptr,
@@ -729,6 +989,17 @@ static qmg_status launch_wilson(const qmg_fine_op_s* op, const void* in, const f
     // 16-bit 18.6 vs 19.6)
     const bool mixed = is16f<LF>() && !is16f<VF>();
     const int near = !mixed && kWilsonSites % ((int64_t)op->dims[0] * op->dims[1]) == 0 ? 2 : 0;
+    if constexpr (!DOT && !is16f<VF>())
+        if (op->csw != 0.0 && use_dirs(op->V, members, false, is16f<LF>())) {
+            const DirArgs A{op->U, op->clov, op->cscale, op->nbr, nullptr, in, in, out, op->V, op->V, op->last,
+                            4.0 + op->m0, 1.0, 0, 0, 0, members, 0, 0};
+            if constexpr (LF != FMT_F64)
+                if (op->link_reals == 12)
+                    return near == 2 ? launch_dirs<LF, VF, 12, false, 2, false, 1>(A, s)
+                                     : launch_dirs<LF, VF, 12, false, 2, false, 0>(A, s);
+            return near == 2 ? launch_dirs<LF, VF, 18, false, 2, false, 1>(A, s)
+                             : launch_dirs<LF, VF, 18, false, 2, false, 0>(A, s);
+        }
 #define QMG_WC_LAUNCH(LR, NEAR)                                                                                    \
     hipLaunchKernelGGL((k_wilson_clover<LF, VF, DOT, LR, NEAR>), dim3(nb, members), dim3(256), 0, s, op->U,       \
                        op->clov, op->cscale, op->nbr, in, in_scale, out, out_scale, op->V, (R)(4.0 + op->m0),    \
@@ -808,40 +1079,41 @@ enum EoPiece {
     EO_COPY = 5       // out = self (re-indexing between half and whole lattice)
 };
 
+template <int LF, int VF, int SELF, bool HOPS, bool INV, int LR = 18>
+static qmg_status launch_eo_piece(const qmg_fine_op_s* op, double coef, int parity, const void* self, int self_full,
+                                  const void* hin, void* out, int out_full, int m, hipStream_t s) {
+    using R = typename FineT<LF>::R;
+    const int64_t Vh = op->V / 2;
+    const int uc = op->csw != 0.0 ? 1 : 0;
+    if constexpr (LF != FMT_F64 && HOPS && LR == 18)
+        if (op->link_reals == 12)
+            return launch_eo_piece<LF, VF, SELF, HOPS, INV, 12>(op, coef, parity, self, self_full, hin, out, out_full, m, s);
+    if constexpr (HOPS)
+        if ((SELF != 2 || uc) && use_dirs(Vh, m, true, is16f<LF>())) {
+            const DirArgs A{op->U_eo, INV ? op->cinv : op->clov_eo, INV ? op->ciscale : op->cscale_eo, op->hnb, op->hsite,
+                            self, hin, out, Vh, op->V, op->last, 4.0 + op->m0, coef, self_full, out_full, parity, m,
+                            0, 0};
+            return launch_dirs<LF, VF, LR, true, SELF, INV, 0>(A, s);
+        }
+    const unsigned nb = (unsigned)(((Vh + 255) / 256 + 7) / 8 * 8);
+    hipLaunchKernelGGL((k_wilson_eo<LF, VF, SELF, HOPS, INV, LR>), dim3(nb, (unsigned)m), dim3(256), 0, s, op->U_eo,
+                       op->clov_eo, op->cscale_eo, op->cinv, op->ciscale, op->hnb, op->hsite, self, hin, out, Vh, op->V,
+                       (R)(4.0 + op->m0), (R)coef, uc, self_full, out_full, op->last, parity, EoScales{});
+    QMG_LAUNCH_CHECK();
+    return QMG_OK;
+}
+
 template <int LF, int VF>
 static qmg_status launch_eo(const qmg_fine_op_s* op, int piece, int parity, const void* self, int self_full,
                             const void* hin, void* out, int out_full, int m, hipStream_t s) {
-    using R = typename FineT<LF>::R;
-    const int64_t Vh = op->V / 2;
-    const unsigned nb = (unsigned)(((Vh + 255) / 256 + 7) / 8 * 8);
-    const R diag = (R)(4.0 + op->m0);
-    const int uc = op->csw != 0.0 ? 1 : 0;
-    const dim3 grid(nb, (unsigned)m), block(256);
-#define QMG_EO_LAUNCH_LR(SELF, HOPS, INV, COEF, LR)                                                              \
-    hipLaunchKernelGGL((k_wilson_eo<LF, VF, SELF, HOPS, INV, LR>), grid, block, 0, s, op->U_eo, op->clov_eo,    \
-                       op->cscale_eo, op->cinv, op->ciscale, op->hnb, op->hsite, self, hin, out, Vh, op->V, diag,  \
-                       (R)(COEF), uc, self_full, out_full, op->last, parity, EoScales{})
-#define QMG_EO_LAUNCH(SELF, HOPS, INV, COEF)                                                                    \
-    do {                                                                                                        \
-        if constexpr (LF != FMT_F64 && HOPS) {                                                                  \
-            if (op->link_reals == 12) QMG_EO_LAUNCH_LR(SELF, HOPS, INV, COEF, 12);                               \
-            else QMG_EO_LAUNCH_LR(SELF, HOPS, INV, COEF, 18);                                                    \
-        } else {                                                                                                \
-            QMG_EO_LAUNCH_LR(SELF, HOPS, INV, COEF, 18);                                                         \
-        }                                                                                                       \
-    } while (0)
     switch (piece) {
-        case EO_HOP_INV: QMG_EO_LAUNCH(0, true, true, 1.0); break;
-        case EO_DIAG_HOP: QMG_EO_LAUNCH(2, true, false, -1.0); break;
-        case EO_INV: QMG_EO_LAUNCH(1, false, true, 0.0); break;
-        case EO_SELF_HOP: QMG_EO_LAUNCH(1, true, false, -1.0); break;
-        case EO_RECON: QMG_EO_LAUNCH(1, true, true, -1.0); break;
-        default: QMG_EO_LAUNCH(1, false, false, 0.0);
+        case EO_HOP_INV: return launch_eo_piece<LF, VF, 0, true, true>(op, 1.0, parity, self, self_full, hin, out, out_full, m, s);
+        case EO_DIAG_HOP: return launch_eo_piece<LF, VF, 2, true, false>(op, -1.0, parity, self, self_full, hin, out, out_full, m, s);
+        case EO_INV: return launch_eo_piece<LF, VF, 1, false, true>(op, 0.0, parity, self, self_full, hin, out, out_full, m, s);
+        case EO_SELF_HOP: return launch_eo_piece<LF, VF, 1, true, false>(op, -1.0, parity, self, self_full, hin, out, out_full, m, s);
+        case EO_RECON: return launch_eo_piece<LF, VF, 1, true, true>(op, -1.0, parity, self, self_full, hin, out, out_full, m, s);
+        default: return launch_eo_piece<LF, VF, 1, false, false>(op, 0.0, parity, self, self_full, hin, out, out_full, m, s);
     }
-#undef QMG_EO_LAUNCH
-#undef QMG_EO_LAUNCH_LR
-    QMG_LAUNCH_CHECK();
-    return QMG_OK;
 }
 
 // One red-black piece with vectors in `vprec` (complex128 for a complex128

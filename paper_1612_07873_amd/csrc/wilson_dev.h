@@ -20,9 +20,21 @@ template <typename R>
 __device__ __forceinline__ cpx<R> cmul(cpx<R> a, cpx<R> b) {
     return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
+__device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// t + a b and t + conj(a) b with the rounding written out, the same in every
+// kernel that forms the sum: the product first, so that the products of a sum
+// do not wait for one another (a chain of multiply-adds into t, two operations
+// fewer, was slower in the one-thread-per-site kernels: FP64 red-black 60 -> 83
+// us on 16^3x32)
 template <typename R>
-__device__ __forceinline__ cpx<R> cmulc(cpx<R> a, cpx<R> b) {  // conj(a) * b
-    return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
+__device__ __forceinline__ cpx<R> cfma(cpx<R> t, cpx<R> a, cpx<R> b) {
+    return {t.re + fmadd(-a.im, b.im, a.re * b.re), t.im + fmadd(a.im, b.re, a.re * b.im)};
+}
+template <typename R>
+__device__ __forceinline__ cpx<R> cfmac(cpx<R> t, cpx<R> a, cpx<R> b) {
+    return {t.re + fmadd(a.im, b.im, a.re * b.re), t.im + fmadd(-a.im, b.re, a.re * b.im)};
 }
 template <typename R> __device__ __forceinline__ cpx<R> ci(cpx<R> a) { return {-a.im, a.re}; }   // i a
 template <typename R> __device__ __forceinline__ cpx<R> cmi(cpx<R> a) { return {a.im, -a.re}; }  // -i a
@@ -89,8 +101,13 @@ __device__ __forceinline__ void load_link_at(cpx<R> u[9], const void* __restrict
         for (int j = 0; j < 3; ++j) {
             const int k = (j + 1) % 3, l = (j + 2) % 3;
             // conj(a_k b_l - a_l b_k)
-            const R re = (u[k].re * u[3 + l].re - u[k].im * u[3 + l].im) - (u[l].re * u[3 + k].re - u[l].im * u[3 + k].im);
-            const R im = (u[k].re * u[3 + l].im + u[k].im * u[3 + l].re) - (u[l].re * u[3 + k].im + u[l].im * u[3 + k].re);
+            R re = u[k].re * u[3 + l].re, im = u[k].re * u[3 + l].im;
+            re = fmadd(-u[k].im, u[3 + l].im, re);
+            re = fmadd(-u[l].re, u[3 + k].re, re);
+            re = fmadd(u[l].im, u[3 + k].im, re);
+            im = fmadd(u[k].im, u[3 + l].re, im);
+            im = fmadd(-u[l].re, u[3 + k].im, im);
+            im = fmadd(-u[l].im, u[3 + k].re, im);
             u[6 + j] = cpx<R>{sg * re, -sg * im};
         }
     }
@@ -133,6 +150,23 @@ __device__ __forceinline__ void load_clover(R d[6], cpx<R> o[15], const void* __
     }
 }
 
+// t = H x for one chirality block H (packed Hermitian 6x6) of a site-local matrix
+template <typename R>
+__device__ __forceinline__ void herm6_mul(cpx<R> out[6], const cpx<R> x[6], const R d[6], const cpx<R> o[15]) {
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        cpx<R> t = {d[i] * x[i].re, d[i] * x[i].im};
+        int k = 0;
+#pragma unroll
+        for (int r = 0; r < 6; ++r)
+#pragma unroll
+            for (int c = r + 1; c < 6; ++c, ++k) {
+                if (r == i) t = cfma(t, o[k], x[c]);
+                if (c == i) t = cfmac(t, o[k], x[r]);
+            }
+        out[i] = t;
+    }
+}
 // acc += H x for a site-local matrix H stored as two packed Hermitian 6x6
 // chirality blocks (the clover term, or the inverse of the site-local block).
 template <int LF, typename R>
@@ -143,20 +177,10 @@ __device__ __forceinline__ void herm_mul_add(cpx<R> acc[12], const cpx<R> x12[12
         R d[6];
         cpx<R> o[15];
         load_clover<LF>(d, o, H, hscale, chi, site, V);
-        const cpx<R>* x = x12 + 6 * chi;
+        cpx<R> t[6];
+        herm6_mul(t, x12 + 6 * chi, d, o);
 #pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            cpx<R> t = {d[i] * x[i].re, d[i] * x[i].im};
-            int k = 0;
-#pragma unroll
-            for (int r = 0; r < 6; ++r)
-#pragma unroll
-                for (int c = r + 1; c < 6; ++c, ++k) {
-                    if (r == i) t = cadd(t, cmul(o[k], x[c]));
-                    if (c == i) t = cadd(t, cmulc(o[k], x[r]));
-                }
-            acc[6 * chi + i] = cadd(acc[6 * chi + i], t);
-        }
+        for (int i = 0; i < 6; ++i) acc[6 * chi + i] = cadd(acc[6 * chi + i], t[i]);
     }
 }
 
@@ -231,10 +255,9 @@ __device__ __forceinline__ void hop_load(cpx<R> p[12], cpx<R> u[9], const void* 
     load_link<LF, LR>(u, U, MU, BACK ? n : site, V, last);
 }
 
-// acc += h * P (x) W psi(n): h = -1/2 is the hop term of Eq. (2)
+// The projected half spinor a of psi(n): the two upper spins of P (x) psi(n)
 template <int MU, bool BACK, typename R>
-__device__ __forceinline__ void hop_apply(cpx<R> acc[12], const cpx<R> p[12], const cpx<R> u[9], const R h = R(-0.5)) {
-    cpx<R> a[2][3];
+__device__ __forceinline__ void hop_project(cpx<R> a[2][3], const cpx<R> p[12]) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         cpx<R> g0, g1;
@@ -242,7 +265,10 @@ __device__ __forceinline__ void hop_apply(cpx<R> acc[12], const cpx<R> p[12], co
         if (!BACK) { a[0][c] = csub(p[c], g0); a[1][c] = csub(p[3 + c], g1); }
         else { a[0][c] = cadd(p[c], g0); a[1][c] = cadd(p[3 + c], g1); }
     }
-    cpx<R> w[2][3];
+}
+// w = W a with W the link (forward) or its adjoint (backward)
+template <bool BACK, typename R>
+__device__ __forceinline__ void hop_link(cpx<R> w[2][3], const cpx<R> a[2][3], const cpx<R> u[9]) {
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -250,20 +276,41 @@ __device__ __forceinline__ void hop_apply(cpx<R> acc[12], const cpx<R> p[12], co
             cpx<R> t = {0, 0};
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                if (!BACK) t = cadd(t, cmul(u[r * 3 + c], a[s][c]));
-                else t = cadd(t, cmulc(u[c * 3 + r], a[s][c]));
+                if (!BACK) t = cfma(t, u[r * 3 + c], a[s][c]);
+                else t = cfmac(t, u[c * 3 + r], a[s][c]);
             }
             w[s][r] = t;
         }
+}
+
+// acc += h * (colour c of one chirality of P (x) W psi(n)) from its upper spins
+// w: CHI = 0 the upper two spins, CHI = 1 the lower two, -+ g_mu^+ w
+template <int MU, bool BACK, int CHI, typename R>
+__device__ __forceinline__ void hop_add_colour(cpx<R> acc[6], const cpx<R> w[2][3], const R h, int c) {
+    cpx<R> l0 = w[0][c], l1 = w[1][c];
+    if (CHI == 1) {
+        gdmul<MU>(l0, l1, w[0][c], w[1][c]);
+        if (!BACK) { l0 = cneg(l0); l1 = cneg(l1); }
+    }
+    acc[c] = {fmadd(h, l0.re, acc[c].re), fmadd(h, l0.im, acc[c].im)};
+    acc[3 + c] = {fmadd(h, l1.re, acc[3 + c].re), fmadd(h, l1.im, acc[3 + c].im)};
+}
+template <int MU, bool BACK, int CHI, typename R>
+__device__ __forceinline__ void hop_add(cpx<R> acc[6], const cpx<R> w[2][3], const R h) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) hop_add_colour<MU, BACK, CHI>(acc, w, h, c);
+}
+
+// acc += h * P (x) W psi(n): h = -1/2 is the hop term of Eq. (2)
+template <int MU, bool BACK, typename R>
+__device__ __forceinline__ void hop_apply(cpx<R> acc[12], const cpx<R> p[12], const cpx<R> u[9], const R h = R(-0.5)) {
+    cpx<R> a[2][3], w[2][3];
+    hop_project<MU, BACK>(a, p);
+    hop_link<BACK>(w, a, u);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        cpx<R> l0, l1;
-        gdmul<MU>(l0, l1, w[0][c], w[1][c]);
-        acc[c].re += h * w[0][c].re; acc[c].im += h * w[0][c].im;
-        acc[3 + c].re += h * w[1][c].re; acc[3 + c].im += h * w[1][c].im;
-        if (!BACK) { l0 = cneg(l0); l1 = cneg(l1); }
-        acc[6 + c].re += h * l0.re; acc[6 + c].im += h * l0.im;
-        acc[9 + c].re += h * l1.re; acc[9 + c].im += h * l1.im;
+        hop_add_colour<MU, BACK, 0>(acc, w, h, c);
+        hop_add_colour<MU, BACK, 1>(acc + 6, w, h, c);
     }
 }
 
