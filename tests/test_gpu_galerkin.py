@@ -127,3 +127,35 @@ def test_ragged_build():
     op = build_coarse_op(Transfer(dims, 12, block, dev(vecs)), fine=FineOp(dims, dev(U), m0, 1.0, True, 'c128'))
     X, Y = op.export()
     assert max(rel_err(host(X), ref.X), rel_err(host(Y), ref.Y)) <= 1e-12
+
+
+@pytest.mark.parametrize('dims,block,nvec,m0,csw,storage,tol', [
+    # one to four column tiles, at both ends of each, and past the last
+    ((4, 4, 4, 6), (2, 2, 2, 3), 1, 0.1, 1.0, 'c128', 1e-12),
+    ((4, 4, 4, 6), (2, 2, 2, 3), 8, 0.1, 1.0, 'c64', 2.0 ** -20),
+    ((4, 4, 4, 6), (2, 2, 2, 3), 9, -0.2, 1.0, 'c128', 1e-12),
+    ((4, 4, 4, 6), (2, 2, 2, 3), 16, -0.2, 0.0, 'c128', 1e-12),
+    ((4, 4, 4, 6), (2, 2, 2, 3), 17, -0.2, 1.0, 'c64', 2.0 ** -20),
+    ((4, 4, 4, 6), (2, 2, 2, 3), 25, -0.2, 1.0, 'c128', 1e-12),
+    ((4, 4, 4, 6), (2, 2, 2, 3), 32, -0.2, 1.0, 'c64', 2.0 ** -20),
+    ((4, 4, 4, 6), (2, 2, 2, 3), 33, -0.2, 1.0, 'c128', 1e-12),
+    # odd numbers of sites per term, and 27 coarse sites (no multiple of the eight XCDs)
+    ((9, 3, 6, 6), (3, 1, 2, 2), 5, -0.2, 1.0, 'c128', 1e-12),
+    # more sites in an aggregate than a work-group lists at a time
+    ((10, 10, 8, 16), (5, 5, 4, 8), 6, -0.2, 1.0, 'c128', 1e-12),
+])
+def test_fine_parent_at_the_edges(dims, block, nvec, m0, csw, storage, tol):
+    """The fine parent's product at the edges of its tiles, chunks and work-group
+    order.  FP64: sums of at most 800 x 6 terms, 1e-12 as above.  FP32 operator:
+    its links and clover entries are rounded to 2^-24 of their size, and a block
+    has norm at most a few times that of its factors: 2^-20."""
+    from paper_1612_07873_amd import FineOp, Transfer, build_coarse_op
+    V = lattice.volume(dims)
+    U = synth.gauge_field(dims, 0.4, 7)
+    A = wilson.clover_field(U, dims, csw)
+    vecs = synth.gaussian((nvec, V, 12), 8, 1)
+    Vb = transfer.block_orthonormalize(vecs, dims, block)
+    ref = coarse.galerkin(coarse.FineParent(U, A, m0, dims), Vb, block)
+    op = build_coarse_op(Transfer(dims, 12, block, dev(vecs)), fine=FineOp(dims, dev(U), m0, csw, True, storage))
+    X, Y = op.export()
+    assert max(rel_err(host(X), ref.X), rel_err(host(Y), ref.Y)) <= tol
