@@ -33,9 +33,18 @@ __device__ __forceinline__ int rev_path(int p) { return p == 0 ? 0 : (((p - 1) &
 // one input channel transports it nine times per site and shares the
 // results among all output channels; a layer with one output channel mixes
 // the input channels first and transports the mixture once per path.  Work-
-// groups cover kPtcSites sites with one thread per (site, path).
+// groups cover kPtcSites sites with one thread per (site, path).  The layer
+// kernels are bound by one thread's chain of latencies and products: 12 us at
+// 4^4, 13 to 15 us at 8^3x16 (C 8; 15 to 18 us with the weights read from global
+// memory where they are used and a channel loaded after the last was mixed).
 constexpr int kPtcSites = 32;
 constexpr int kPtcFanThreads = kPtcSites * 9;
+// Strides in LDS, in float2, odd so that lanes on different sites, slices of
+// sites or channels read different banks.
+constexpr int kPtcSiteLd = 9 * 12 + 1;              // a site's nine transports
+constexpr int kPtcMixLd = 13;                       // a site of one channel
+constexpr int kPtcChanLd = kPtcSites * kPtcMixLd + 1;
+constexpr int kPtcChLoads = (8 * kPtcSites * 12 + kPtcFanThreads - 1) / kPtcFanThreads;   // eight channels
 
 // T_p applied to the spinor v already read at the neighbour n of x
 __device__ __forceinline__ void transport_vals(float2 t[12], const float2 v[12], const float2* __restrict__ U,
@@ -71,6 +80,28 @@ __device__ __forceinline__ int64_t path_site(const int* __restrict__ nbr, int64_
     return p == 0 ? x : nbr[x * 8 + 2 * ((p - 1) >> 1) + ((p - 1) & 1)];
 }
 
+// The n weights of a launch on their way to LDS: loaded first, all at once, and
+// stored when the work-group's own field values are on their way too (one load
+// after the other would add a memory latency each).  J work-group sizes cover n.
+template <int J>
+__device__ __forceinline__ void weights_load(float2 (&w)[J], const float2* __restrict__ W, int n) {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int i = (int)threadIdx.x + j * kPtcFanThreads;
+        w[j] = W[i < n ? i : n - 1];
+    }
+}
+template <int J>
+__device__ __forceinline__ void weights_store(float2* Ws, const float2 (&w)[J], int n, int row, int ld) {   // rows ld apart
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int i = (int)threadIdx.x + j * kPtcFanThreads;
+        if (i < n) Ws[(i / row) * ld + i % row] = w[j];
+    }
+}
+constexpr int kPtcMaxHidden = 16;
+constexpr int kPtcWLoads = (9 * kPtcMaxHidden * 16 + kPtcFanThreads - 1) / kPtcFanThreads;
+
 // One transported input channel h, C output channels:
 //   forward (first layer):           out_a = sum_p W1[p][a][0] (T_p h)
 //   ADJ (data gradient of the second): out_b = sum_p W2[p][0][b]^+ (T_{rev p} h)
@@ -80,9 +111,13 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_fan_out(float2* __restri
                                                                 const float2* __restrict__ W,
                                                                 const float2* __restrict__ U,
                                                                 const int* __restrict__ nbr, int64_t V, int C) {
-    __shared__ float2 tp[kPtcSites][9][12];
+    __shared__ float2 tp[kPtcSites * kPtcSiteLd];
+    extern __shared__ __align__(16) unsigned char smem[];
+    float2* Ws = reinterpret_cast<float2*>(smem);   // [9][C][16]
     const int64_t x0 = (int64_t)blockIdx.x * kPtcSites;
     const int t = threadIdx.x;
+    float2 wv[kPtcWLoads];
+    weights_load(wv, W, 9 * C * 16);
     {
         const int sl = t / 9, p = t - (t / 9) * 9;
         const int64_t x = x0 + sl;
@@ -94,9 +129,10 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_fan_out(float2* __restri
             for (int f = 0; f < 12; ++f) v[f] = h[n * 12 + f];
             transport_vals(w, v, U, V, x, n, q);
 #pragma unroll
-            for (int f = 0; f < 12; ++f) tp[sl][p][f] = w[f];
+            for (int f = 0; f < 12; ++f) tp[sl * kPtcSiteLd + p * 12 + f] = w[f];
         }
     }
+    weights_store(Ws, wv, 9 * C * 16, 9 * C * 16, 0);
     __syncthreads();
     for (int idx = t; idx < kPtcSites * C; idx += kPtcFanThreads) {
         const int sl = idx % kPtcSites, a = idx / kPtcSites;
@@ -106,26 +142,21 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_fan_out(float2* __restri
 #pragma unroll
         for (int f = 0; f < 12; ++f) acc[f] = make_float2(0, 0);
         for (int p = 0; p < 9; ++p) {
-            const float2* w = W + ((int64_t)p * C + a) * 16;
+            const float2* w = Ws + (p * C + a) * 16;
+            float2 v[12];
+#pragma unroll
+            for (int f = 0; f < 12; ++f) v[f] = tp[sl * kPtcSiteLd + p * 12 + f];
 #pragma unroll
             for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    float re = acc[sp * 3 + c].x, im = acc[sp * 3 + c].y;
+                for (int q = 0; q < 4; ++q) {
+                    // W[sp][q], or conj(W[q][sp])
+                    const float2 m = ADJ ? make_float2(w[q * 4 + sp].x, -w[q * 4 + sp].y) : w[sp * 4 + q];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float2 v = tp[sl][p][q * 3 + c];
-                        if (ADJ) {   // conj(W[q][sp]) v
-                            const float2 m = w[q * 4 + sp];
-                            re += m.x * v.x + m.y * v.y;
-                            im += m.x * v.y - m.y * v.x;
-                        } else {
-                            const float2 m = w[sp * 4 + q];
-                            re += m.x * v.x - m.y * v.y;
-                            im += m.x * v.y + m.y * v.x;
-                        }
+                    for (int c = 0; c < 3; ++c) {
+                        acc[sp * 3 + c].x += m.x * v[q * 3 + c].x - m.y * v[q * 3 + c].y;
+                        acc[sp * 3 + c].y += m.x * v[q * 3 + c].y + m.y * v[q * 3 + c].x;
                     }
-                    acc[sp * 3 + c] = make_float2(re, im);
                 }
         }
 #pragma unroll
@@ -139,34 +170,50 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_fan_in(float2* __restric
                                                                const float2* __restrict__ U,
                                                                const int* __restrict__ nbr, int64_t V, int C) {
     __shared__ float2 cp[kPtcSites][9][12];
+    extern __shared__ __align__(16) unsigned char smem[];
+    float2* Ws = reinterpret_cast<float2*>(smem);   // [9][C * 16 + 2]: the nine paths of a wave in different banks
     const int64_t x0 = (int64_t)blockIdx.x * kPtcSites;
     const int t = threadIdx.x;
+    const int wld = C * 16 + 2;
+    float2 wv[kPtcWLoads];
+    weights_load(wv, W, 9 * C * 16);
     {
         const int sl = t / 9, p = t - (t / 9) * 9;
-        const int64_t x = x0 + sl;
-        if (x < V) {
+        const int64_t x = x0 + sl < V ? x0 + sl : V - 1;   // past the end the last site, not used
+        {
             const int64_t n = path_site(nbr, x, p);
             float2 g[12];
 #pragma unroll
             for (int f = 0; f < 12; ++f) g[f] = make_float2(0, 0);
-            for (int b = 0; b < C; ++b) {
-                const float2* w = W + ((int64_t)p * C + b) * 16;
-                float2 v[12];
+            // the next channel is loaded while one is mixed; two buffers by turns
+            auto load = [&](float2 (&v)[12], int b) {
+                const float2* hb = h + ((int64_t)(b < C ? b : C - 1) * V + n) * 12;
 #pragma unroll
-                for (int f = 0; f < 12; ++f) v[f] = h[((int64_t)b * V + n) * 12 + f];
+                for (int f = 0; f < 12; ++f) v[f] = hb[f];
+            };
+            auto mix = [&](const float2 (&v)[12], int b) {
+                const float2* w = Ws + p * wld + b * 16;
 #pragma unroll
                 for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        float re = g[sp * 3 + c].x, im = g[sp * 3 + c].y;
+                    for (int q = 0; q < 4; ++q) {
+                        const float2 m = w[sp * 4 + q];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const float2 m = w[sp * 4 + q], vv = v[q * 3 + c];
-                            re += m.x * vv.x - m.y * vv.y;
-                            im += m.x * vv.y + m.y * vv.x;
+                        for (int c = 0; c < 3; ++c) {
+                            g[sp * 3 + c].x += m.x * v[q * 3 + c].x - m.y * v[q * 3 + c].y;
+                            g[sp * 3 + c].y += m.x * v[q * 3 + c].y + m.y * v[q * 3 + c].x;
                         }
-                        g[sp * 3 + c] = make_float2(re, im);
                     }
+            };
+            float2 va[12], vb[12];
+            load(va, 0);
+            weights_store(Ws, wv, 9 * C * 16, C * 16, wld);
+            __syncthreads();
+            for (int b = 0; b < C; b += 2) {
+                load(vb, b + 1);
+                mix(va, b);
+                load(va, b + 2);
+                if (b + 1 < C) mix(vb, b + 1);
             }
             float2 w2[12];
             transport_vals(w2, g, U, V, x, n, p);
@@ -199,9 +246,13 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_fan_in(float2* __restric
 // of Q slices of the chunk's sites (Q * 9C <= threads): per site and colour
 // it reads 4 + 4 operands for 16 products, sums the chunk in FP32 and adds
 // the chunk sums to FP64 totals in registers.  At the end the Q slices are
-// added in a fixed order in LDS and the work-group's sums go to
+// added in a fixed order and the work-group's sums go to
 // part[blk][9C][32], which a second kernel sums over work-groups in a fixed
-// order.
+// order.  Bound: one chunk's chain of memory latencies (neighbour, field and
+// link, LDS) with 4.5 waves on a CU; so a work-group per chunk up to
+// kPtcMaxBlocks, the chunk's channels loaded eight at a time, odd strides in
+// LDS.  8^3x16, C 8: 125 -> 17.6 us (an eighth as many work-groups
+// of eight chunks each, strides of 12 that put 32 lanes on a bank), 4^4 16 us.
 template <bool TR_LEFT>
 __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_wgrad_fan(double* __restrict__ part,
                                                                   const float2* __restrict__ tr,
@@ -209,8 +260,8 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_wgrad_fan(double* __rest
                                                                   const float2* __restrict__ U,
                                                                   const int* __restrict__ nbr, int64_t V, int C) {
     extern __shared__ __align__(16) unsigned char smem[];
-    float2 (*tp)[9][12] = reinterpret_cast<float2 (*)[9][12]>(smem);
-    float2* ms = reinterpret_cast<float2*>(smem + sizeof(float2) * kPtcSites * 9 * 12);   // [C][kPtcSites][12]
+    float2* tp = reinterpret_cast<float2*>(smem);   // [kPtcSites][9][12], strides as above
+    float2* ms = tp + kPtcSites * kPtcSiteLd;       // [C][kPtcSites][12]
     const int t = threadIdx.x;
     int Q = kPtcSites;
     while (Q * C > kPtcSites) Q >>= 1;   // 9 C Q <= 9 kPtcSites = the work-group size
@@ -224,6 +275,27 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_wgrad_fan(double* __rest
     const int64_t nchunks = (V + kPtcSites - 1) / kPtcSites;
     for (int64_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
         const int64_t x0 = ch * kPtcSites;
+        // the channels of the chunk, the loads of eight channels in flight at a time
+        auto chan_load = [&](float2 (&v)[kPtcChLoads], int j0) {
+#pragma unroll
+            for (int j = 0; j < kPtcChLoads; ++j) {
+                const int i1 = t + (j0 + j) * kPtcFanThreads, idx = i1 < C * kPtcSites * 12 ? i1 : C * kPtcSites * 12 - 1;
+                const int f = idx % 12, sl = (idx / 12) % kPtcSites, kk = idx / (12 * kPtcSites);
+                const int64_t x = x0 + sl < V ? x0 + sl : V - 1;
+                v[j] = mc[((int64_t)kk * V + x) * 12 + f];
+            }
+        };
+        auto chan_store = [&](const float2 (&v)[kPtcChLoads], int j0) {
+#pragma unroll
+            for (int j = 0; j < kPtcChLoads; ++j) {
+                const int idx = t + (j0 + j) * kPtcFanThreads;
+                const int f = idx % 12, sl = (idx / 12) % kPtcSites, kk = idx / (12 * kPtcSites);
+                if (idx < C * kPtcSites * 12)
+                    ms[kk * kPtcChanLd + sl * kPtcMixLd + f] = x0 + sl < V ? v[j] : make_float2(0, 0);
+            }
+        };
+        float2 mv[kPtcChLoads];
+        chan_load(mv, 0);
         __syncthreads();   // the previous chunk's LDS reads are done
         {
             const int sl = t / 9, q = t - (t / 9) * 9;
@@ -241,12 +313,12 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_wgrad_fan(double* __rest
                 for (int f = 0; f < 12; ++f) w[f] = make_float2(0, 0);
             }
 #pragma unroll
-            for (int f = 0; f < 12; ++f) tp[sl][q][f] = w[f];
+            for (int f = 0; f < 12; ++f) tp[sl * kPtcSiteLd + q * 12 + f] = w[f];
         }
-        for (int idx = t; idx < C * kPtcSites * 12; idx += kPtcFanThreads) {
-            const int f = idx % 12, sl = (idx / 12) % kPtcSites, kk = idx / (12 * kPtcSites);
-            const int64_t x = x0 + sl;
-            ms[idx] = x < V ? mc[((int64_t)kk * V + x) * 12 + f] : make_float2(0, 0);
+        chan_store(mv, 0);
+        for (int j0 = kPtcChLoads; j0 * kPtcFanThreads < C * kPtcSites * 12; j0 += kPtcChLoads) {
+            chan_load(mv, j0);
+            chan_store(mv, j0);
         }
         __syncthreads();
         if (active) {
@@ -255,8 +327,8 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_wgrad_fan(double* __rest
             for (int e = 0; e < 16; ++e) sr[e] = si[e] = 0.0f;
             for (int i = 0; i < S; ++i) {
                 const int sl = quarter * S + i;
-                const float2* m = ms + ((int64_t)k * kPtcSites + sl) * 12;
-                const float2* tq = tp[sl][p];
+                const float2* m = ms + k * kPtcChanLd + sl * kPtcMixLd;
+                const float2* tq = tp + sl * kPtcSiteLd + p * 12;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     float2 L[4], R[4];
@@ -281,33 +353,54 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_wgrad_fan(double* __rest
             }
         }
     }
-    // the Q slices of each pair, added in slice order, then the work-group's sums
-    __syncthreads();
-    double* red = reinterpret_cast<double*>(smem);   // [9C][32]
-    for (int qd = 0; qd < Q; ++qd) {
-        if (active && quarter == qd)
+    // the Q slices of a pair are neighbouring lanes; then the work-group's sums,
+    // rows of 33 in LDS so that the pairs' writes fall into different banks
+    for (int o = 1; o < Q; o <<= 1)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                double* d = red + pair * 32 + 2 * e;
-                d[0] = qd ? d[0] + acc[e][0] : acc[e][0];
-                d[1] = qd ? d[1] + acc[e][1] : acc[e][1];
-            }
-        __syncthreads();
-    }
-    for (int i = t; i < 9 * C * 32; i += kPtcFanThreads) part[(int64_t)blockIdx.x * (9 * C) * 32 + i] = 2.0 * red[i];
+        for (int e = 0; e < 16; ++e) {
+            acc[e][0] += __shfl_xor(acc[e][0], o, 64);
+            acc[e][1] += __shfl_xor(acc[e][1], o, 64);
+        }
+    __syncthreads();
+    double* red = reinterpret_cast<double*>(smem);   // [9C][33]
+    if (active && quarter == 0)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            red[pair * 33 + 2 * e] = acc[e][0];
+            red[pair * 33 + 2 * e + 1] = acc[e][1];
+        }
+    __syncthreads();
+    for (int i = t; i < 9 * C * 32; i += kPtcFanThreads)
+        part[(int64_t)blockIdx.x * (9 * C) * 32 + i] = 2.0 * red[(i >> 5) * 33 + (i & 31)];
 }
 
-// G[combo][16] += sum over blocks (fixed order)
-__global__ void k_ptc_wgrad_final(float2* __restrict__ G, const double* __restrict__ part, int nblk, int ncombo) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= ncombo * 16) return;
-    double re = 0, im = 0;
-    for (int k = 0; k < nblk; ++k) {
-        re += part[((int64_t)k * ncombo) * 32 + 2 * i];
-        im += part[((int64_t)k * ncombo) * 32 + 2 * i + 1];
+// G[combo][16] += sum over blocks (fixed order): a work-group takes sixteen
+// entries, thread (slice, entry) adds every sixteenth block's sum, and the
+// slices are added in order.
+__global__ __launch_bounds__(256) void k_ptc_wgrad_final(float2* __restrict__ G, const double* __restrict__ part,
+                                                         int nblk, int ncombo) {
+    __shared__ double2 red[16][16];
+    const int e = threadIdx.x & 15, sl = threadIdx.x >> 4;
+    const int i = blockIdx.x * 16 + e;   // ncombo * 16 entries, one per thread of a slice
+    const double2* p = reinterpret_cast<const double2*>(part) + i;
+    double2 a = make_double2(0, 0);
+#pragma unroll 8
+    for (int k = sl; k < nblk; k += 16) {
+        const double2 v = p[(int64_t)k * ncombo * 16];
+        a.x += v.x;
+        a.y += v.y;
     }
-    G[i].x += (float)re;
-    G[i].y += (float)im;
+    red[sl][e] = a;
+    __syncthreads();
+    if (sl) return;
+    a = make_double2(0, 0);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        a.x += red[k][e].x;
+        a.y += red[k][e].y;
+    }
+    G[i].x += (float)a.x;
+    G[i].y += (float)a.y;
 }
 
 // per-block partials of |e|^2 (slot 0) and |y - e|^2 (slot 1)
@@ -334,24 +427,35 @@ __global__ __launch_bounds__(256) void k_ptc_loss_part(double* __restrict__ part
     }
 }
 
-// loss[0] += |y-e|^2/|e|^2 ; loss[1] = |e|^2
-__global__ void k_ptc_loss_final(double* __restrict__ loss, const double* __restrict__ part, int nblk) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double ee = 0, dd = 0;
-    for (int k = 0; k < nblk; ++k) {
-        ee += part[2 * k];
-        dd += part[2 * k + 1];
-    }
-    loss[1] = ee;
-    loss[0] += ee > 0 ? dd / ee : 0.0;
-}
-
-// D = (y - e)/|e|^2
-__global__ void k_ptc_dloss(float2* __restrict__ D, const float2* __restrict__ y, const float2* __restrict__ e,
-                            const double* __restrict__ loss, int64_t n) {
+// D = (y - e)/|e|^2, times gamma5 if G5.  Every work-group adds the partials of
+// both norms itself, in the same order (at most kPtcMaxBlocks pairs from the
+// L2); the first one does loss[0] += |y-e|^2/|e|^2, loss[1] = |e|^2.
+template <bool G5>
+__global__ __launch_bounds__(256) void k_ptc_dloss(float2* __restrict__ D, const float2* __restrict__ y,
+                                                   const float2* __restrict__ e, double* __restrict__ loss,
+                                                   const double2* __restrict__ part, int nblk, int64_t n) {
+    __shared__ double2 red[4];
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    double ee = 0, dd = 0;
+    for (int k = threadIdx.x; k < nblk; k += 256) {
+        ee += part[k].x;
+        dd += part[k].y;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        ee += __shfl_down(ee, o, 64);
+        dd += __shfl_down(dd, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = make_double2(ee, dd);
+    __syncthreads();
+    ee = red[0].x + red[1].x + red[2].x + red[3].x;
+    dd = red[0].y + red[1].y + red[2].y + red[3].y;
+    if (i == 0) {
+        loss[1] = ee;
+        loss[0] += ee > 0 ? dd / ee : 0.0;
+    }
     if (i >= n) return;
-    const float inv = loss[1] > 0 ? (float)(1.0 / loss[1]) : 0.0f;
+    float inv = ee > 0 ? (float)(1.0 / ee) : 0.0f;
+    if (G5 && i % 12 >= 6) inv = -inv;
     D[i] = make_float2((y[i].x - e[i].x) * inv, (y[i].y - e[i].y) * inv);
 }
 
@@ -442,7 +546,8 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_mix(float2* __restrict__
     __shared__ float2 ks[81 * 16];
     const int64_t x0 = (int64_t)blockIdx.x * kPtcSites;
     const int t = threadIdx.x;
-    for (int i = t; i < 81 * 16; i += kPtcFanThreads) ks[i] = K[i];
+    float2 kv[(81 * 16 + kPtcFanThreads - 1) / kPtcFanThreads];
+    weights_load(kv, K, 81 * 16);
     const int pq = t / kPtcSites, sl = t - pq * kPtcSites;
     const int64_t x = x0 + sl;
     {
@@ -456,6 +561,7 @@ __global__ __launch_bounds__(kPtcFanThreads) void k_ptc_mix(float2* __restrict__
 #pragma unroll
         for (int f = 0; f < 12; ++f) tp[pq][f][sl] = w[f];
     }
+    weights_store(ks, kv, 81 * 16, 81 * 16, 0);
     __syncthreads();
     if (x >= V) return;
     // thread (p, site): g_p = sum_q K[p][q] T_q r
@@ -534,9 +640,9 @@ static qmg_status ptc_forward_layers(qmg_ptc t, const void* r, void* y, hipStrea
     const int64_t V = t->V;
     const unsigned gx = (unsigned)((V + kPtcSites - 1) / kPtcSites);
     const float2* U = (const float2*)t->op->U;
-    hipLaunchKernelGGL(k_ptc_fan_out<false>, dim3(gx), dim3(kPtcFanThreads), 0, s, t->h1, (const float2*)r, t->W1, U,
+    hipLaunchKernelGGL(k_ptc_fan_out<false>, dim3(gx), dim3(kPtcFanThreads), sizeof(float2) * 9 * t->C * 16, s, t->h1, (const float2*)r, t->W1, U,
                        t->op->nbr, V, t->C);
-    hipLaunchKernelGGL(k_ptc_fan_in, dim3(gx), dim3(kPtcFanThreads), 0, s, (float2*)y, t->h1, t->W2, U, t->op->nbr, V,
+    hipLaunchKernelGGL(k_ptc_fan_in, dim3(gx), dim3(kPtcFanThreads), sizeof(float2) * 9 * (t->C * 16 + 2), s, (float2*)y, t->h1, t->W2, U, t->op->nbr, V,
                        t->C);
     QMG_LAUNCH_CHECK();
     return QMG_OK;
@@ -580,7 +686,7 @@ extern "C" qmg_status qmg_ptc_create(qmg_fine_op links, int hidden, void* stream
     if (!links) return fail(QMG_ERR_ARG, "ptc_create: links is NULL");
     if (links->storage != QMG_C64 || links->link_reals != 18)
         return fail(QMG_ERR_PREC, "ptc_create: the operator must use complex64 storage of all 18 link reals");
-    if (hidden < 1 || hidden > 16) return fail(QMG_ERR_ARG, "ptc_create: hidden channels %d outside [1,16]", hidden);
+    if (hidden < 1 || hidden > kPtcMaxHidden) return fail(QMG_ERR_ARG, "ptc_create: hidden channels %d outside [1,16]", hidden);
     hipStream_t s = as_stream(stream);
     auto* t = new qmg_ptc_s();
     t->op = links;
@@ -676,9 +782,8 @@ extern "C" qmg_status qmg_ptc_accumulate_grad(qmg_ptc t, const void* r, const vo
     QMG_TRY(ptc_forward_layers(t, r, t->y, s));
     const int nb = ptc_blocks(n);
     hipLaunchKernelGGL(k_ptc_loss_part, dim3(nb), dim3(256), 0, s, t->part, t->y, (const float2*)e, n);
-    hipLaunchKernelGGL(k_ptc_loss_final, dim3(1), dim3(64), 0, s, t->loss, t->part, nb);
-    hipLaunchKernelGGL(k_ptc_dloss, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, t->D2, t->y,
-                       (const float2*)e, t->loss, n);
+    hipLaunchKernelGGL(k_ptc_dloss<false>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, t->D2, t->y,
+                       (const float2*)e, t->loss, (const double2*)t->part, nb, n);
     return ptc_backward(t, r, s);
 }
 
@@ -687,19 +792,17 @@ extern "C" qmg_status qmg_ptc_accumulate_grad_residual(qmg_ptc t, const void* r,
     hipStream_t s = as_stream(stream);
     const int64_t n = t->V * 12;
     QMG_TRY(ptc_forward_layers(t, r, t->y, s));
-    // t1 = M y ; loss += |M y - r|^2/|r|^2 ; t2 = (M y - r)/|r|^2 = dL/d(My)*
+    // t1 = M y ; loss += |M y - r|^2/|r|^2 ; t2 = gamma5 (M y - r)/|r|^2 = gamma5 dL/d(My)*
     QMG_TRY(qmg_wilson_clover_dslash(t->op, t->y, t->t1, 1, QMG_C64, stream));
     const int nb = ptc_blocks(n);
     hipLaunchKernelGGL(k_ptc_loss_part, dim3(nb), dim3(256), 0, s, t->part, t->t1, (const float2*)r, n);
-    hipLaunchKernelGGL(k_ptc_loss_final, dim3(1), dim3(64), 0, s, t->loss, t->part, nb);
-    hipLaunchKernelGGL(k_ptc_dloss, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, t->t2, t->t1,
-                       (const float2*)r, t->loss, n);
-    // D2 = M^+ t2 = gamma5 M gamma5 t2
     const unsigned g = (unsigned)((n + 255) / 256);
-    hipLaunchKernelGGL(k_gamma5_scale, dim3(g), dim3(256), 0, s, t->t1, t->t2, t->loss, 0, n);
+    hipLaunchKernelGGL(k_ptc_dloss<true>, dim3(g), dim3(256), 0, s, t->t2, t->t1, (const float2*)r, t->loss,
+                       (const double2*)t->part, nb, n);
     QMG_LAUNCH_CHECK();
-    QMG_TRY(qmg_wilson_clover_dslash(t->op, t->t1, t->t2, 1, QMG_C64, stream));
-    hipLaunchKernelGGL(k_gamma5_scale, dim3(g), dim3(256), 0, s, t->D2, t->t2, t->loss, 0, n);
+    // D2 = M^+ dL/d(My)* = gamma5 M t2
+    QMG_TRY(qmg_wilson_clover_dslash(t->op, t->t2, t->t1, 1, QMG_C64, stream));
+    hipLaunchKernelGGL(k_gamma5_scale, dim3(g), dim3(256), 0, s, t->D2, t->t1, t->loss, 0, n);
     QMG_LAUNCH_CHECK();
     return ptc_backward(t, r, s);
 }
@@ -710,8 +813,10 @@ qmg_status ptc_backward(qmg_ptc t, const void* r, hipStream_t s) {
     const float2* U = (const float2*)t->op->U;
     const int* nbr = t->op->nbr;
     const int C = t->C;
-    const int gb = ptc_blocks(V);
-    const size_t lds = sizeof(float2) * kPtcSites * 12 * (9 + C);
+    // a work-group per chunk of sites while there are fewer than kPtcMaxBlocks
+    const int64_t chunks = (V + kPtcSites - 1) / kPtcSites;
+    const int gb = (int)(chunks > kPtcMaxBlocks ? kPtcMaxBlocks : chunks);
+    const size_t lds = sizeof(float2) * (kPtcSites * kPtcSiteLd + C * kPtcChanLd);
     if (lds > 65536) {
         QMG_HIP(hipFuncSetAttribute((const void*)k_ptc_wgrad_fan<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         QMG_HIP(hipFuncSetAttribute((const void*)k_ptc_wgrad_fan<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -719,13 +824,13 @@ qmg_status ptc_backward(qmg_ptc t, const void* r, hipStream_t s) {
     // second layer (C -> 1): weight gradient, then D1 = dL/dh1*
     hipLaunchKernelGGL(k_ptc_wgrad_fan<true>, dim3(gb), dim3(kPtcFanThreads), lds, s, t->part, t->D2, t->h1, U, nbr, V,
                        C);
-    hipLaunchKernelGGL(k_ptc_wgrad_final, dim3((9 * C * 16 + 255) / 256), dim3(256), 0, s, t->G2, t->part, gb, 9 * C);
+    hipLaunchKernelGGL(k_ptc_wgrad_final, dim3(9 * C), dim3(256), 0, s, t->G2, t->part, gb, 9 * C);
     const unsigned gx = (unsigned)((V + kPtcSites - 1) / kPtcSites);
-    hipLaunchKernelGGL(k_ptc_fan_out<true>, dim3(gx), dim3(kPtcFanThreads), 0, s, t->D1, t->D2, t->W2, U, nbr, V, C);
+    hipLaunchKernelGGL(k_ptc_fan_out<true>, dim3(gx), dim3(kPtcFanThreads), sizeof(float2) * 9 * C * 16, s, t->D1, t->D2, t->W2, U, nbr, V, C);
     // first layer (1 -> C): weight gradient against the input r
     hipLaunchKernelGGL(k_ptc_wgrad_fan<false>, dim3(gb), dim3(kPtcFanThreads), lds, s, t->part, (const float2*)r,
                        t->D1, U, nbr, V, C);
-    hipLaunchKernelGGL(k_ptc_wgrad_final, dim3((9 * C * 16 + 255) / 256), dim3(256), 0, s, t->G1, t->part, gb, 9 * C);
+    hipLaunchKernelGGL(k_ptc_wgrad_final, dim3(9 * C), dim3(256), 0, s, t->G1, t->part, gb, 9 * C);
     QMG_LAUNCH_CHECK();
     return QMG_OK;
 }

@@ -209,3 +209,31 @@ def test_recorded_smoother_inputs_match_the_oracle_kcycle():
     err = np.linalg.norm(Rh[1] - r2) / np.linalg.norm(r2)
     print('post-smoother input vs oracle K-cycle: %.2e' % err)
     assert err <= 1e-4
+
+
+@pytest.mark.parametrize('dims,C', [
+    ((3, 5, 3, 7), 1),       # 315 sites: the last work-group's chunk is ragged; 32 slices of a channel
+    ((3, 5, 3, 7), 3),       # pairs that do not fill a work-group; eight slices
+    ((2, 3, 3, 3), 9),       # past the channels loaded at once; two slices
+    ((4, 4, 4, 4), 16),      # the largest hidden layer
+    ((12, 12, 12, 10), 2),   # 540 chunks: work-groups with a second one
+])
+def test_gradients_at_the_edges_of_the_chunks(dims, C):
+    """Both weight gradients and the loss at the edges of their kernels' splits.
+    FP32 fields, products and chunk sums: a field entry is a sum of at most 9 C
+    spin-colour products (relative error some 2^-24 sqrt(9 16 16) = 3e-6 at C = 16),
+    the lattice sums are FP64: 1e-5 as above."""
+    from paper_1612_07873_amd import PTC, FineOp
+    V = lattice.volume(dims)
+    U = synth.gauge_field(dims, 0.4, 12)
+    net = PTC(FineOp(dims, dev(U), -0.2, 1.0, True, 'c64'), C)
+    W1, W2 = weights(C, 13)
+    net.set_weights(dev(W1, torch.complex64), dev(W2, torch.complex64))
+    q = lambda a: a.astype(np.complex64).astype(np.complex128)
+    r, e = synth.gaussian((V, 4, 3), 14, 2), synth.gaussian((V, 4, 3), 15, 2)
+    net.zero_grad()
+    net.accumulate(dev(r, torch.complex64), dev(e, torch.complex64))
+    G1, G2, L = net.grad()
+    Lo, (G1o, G2o) = optc.loss_and_grads([q(W1), q(W2)], [(q(r), q(e))], U, dims)
+    assert abs(L - Lo) <= 1e-5 * Lo
+    assert rel_err(host(G1), G1o) <= 1e-5 and rel_err(host(G2), G2o) <= 1e-5
