@@ -160,3 +160,20 @@ def test_batched_stencil_equals_the_single_one(cdims, N, nrhs, launches, storage
         ue = ud[:, :V // 2].contiguous()
         y = g.schur(ue)
         assert all(torch.equal(y[k], g.schur(ue[k].contiguous())) for k in range(nrhs))
+
+
+@pytest.mark.parametrize('N', [16, 32, 48, 64])
+@pytest.mark.parametrize('nrhs,storage', [(8, 'h16'), (16, 'b16'), (64, 'h16')])
+def test_batch_rounded_in_place_equals_rows_rounded_one_by_one(N, nrhs, storage):
+    """The complex64 batch's own rounding to 16 bits against the row-by-row
+    quantiser: the same codes and scales, so the same outputs to the bit.  135
+    sites: the last work-group of 8 members is half empty.  One row is zero."""
+    from paper_1612_07873_amd import CoarseOp, quantize_sites
+    cdims = (3, 3, 3, 5)
+    V = lattice.volume(cdims)
+    op = CoarseOp(cdims, dev(synth.gaussian((V, N, N), 1, 2)), dev(synth.gaussian((8, V, N, N), 2, 2)), storage)
+    u = dev(synth.gaussian((nrhs, V, N), 3, 2), torch.complex64)
+    u[nrhs - 1, V - 1] = 0
+    q, sc = quantize_sites(u.permute(1, 0, 2).contiguous().reshape(V * nrhs, N), storage)
+    ref = op.apply_mrhs(q.reshape(V, nrhs, N), sc.reshape(V, nrhs)).permute(1, 0, 2)
+    assert torch.equal(torch.view_as_real(op.apply_mrhs_c64(u)), torch.view_as_real(ref.contiguous()))
