@@ -30,11 +30,11 @@ __device__ __forceinline__ double fmadd(double a, double b, double c) { return _
 // us on 16^3x32)
 template <typename R>
 __device__ __forceinline__ cpx<R> cfma(cpx<R> t, cpx<R> a, cpx<R> b) {
-    return {t.re + fmadd(-a.im, b.im, a.re * b.re), t.im + fmadd(a.im, b.re, a.re * b.im)};
+    return {t.re + fmadd(a.re, b.re, -(a.im * b.im)), t.im + fmadd(a.re, b.im, a.im * b.re)};
 }
 template <typename R>
 __device__ __forceinline__ cpx<R> cfmac(cpx<R> t, cpx<R> a, cpx<R> b) {
-    return {t.re + fmadd(a.im, b.im, a.re * b.re), t.im + fmadd(-a.im, b.re, a.re * b.im)};
+    return {t.re + fmadd(a.re, b.re, a.im * b.im), t.im + fmadd(a.re, b.im, -(a.im * b.re))};
 }
 template <typename R> __device__ __forceinline__ cpx<R> ci(cpx<R> a) { return {-a.im, a.re}; }   // i a
 template <typename R> __device__ __forceinline__ cpx<R> cmi(cpx<R> a) { return {a.im, -a.re}; }  // -i a
