@@ -123,7 +123,7 @@ __global__ __launch_bounds__(256) void k_wilson_clover(const void* __restrict__ 
             cpx<R> p[12];
             load_spinor<VF>(p, in, in_scale, site + vo);
 #pragma unroll
-            for (int f = 0; f < 12; ++f) acc[f] = {diag * p[f].re, diag * p[f].im};
+            for (int f = 0; f < 12; ++f) acc[f] = cscale_add(cpx<R>{R(0), R(0)}, diag, p[f]);
             if (use_clover) herm_mul_add<LF>(acc, p, clov, cscale, site, V);
         }
         hop_apply<0, false>(acc, pa, ua);
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256) void k_wilson_clover(const void* __restrict__ 
         cpx<R> pa[12], ua[9];
         load_spinor<VF>(pa, in, in_scale, site + vo);
 #pragma unroll
-        for (int f = 0; f < 12; ++f) acc[f] = {diag * pa[f].re, diag * pa[f].im};
+        for (int f = 0; f < 12; ++f) acc[f] = cscale_add(cpx<R>{R(0), R(0)}, diag, pa[f]);
         if (use_clover) herm_mul_add<LF>(acc, pa, clov, cscale, site, V);
         hop_load<0, false, LF, VF, LR>(pa, ua, in, in_scale, U, V, site, nb[0], vo, last);
         hop_apply<0, false>(acc, pa, ua);
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256) void k_wilson_clover(const void* __restrict__ 
 #pragma unroll
             for (int f = 0; f < 12; ++f) p[f] = sh[f * kWilsonSites + t];
 #pragma unroll
-            for (int f = 0; f < 12; ++f) acc[f] = {fmadd(diag, p[f].re, acc[f].re), fmadd(diag, p[f].im, acc[f].im)};
+            for (int f = 0; f < 12; ++f) acc[f] = cscale_add(acc[f], diag, p[f]);
             if (use_clover) herm_mul_add<LF>(acc, p, clov, cscale, site, V);
         }
         hop_apply<1, false>(acc, pa, ua);
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256) void k_wilson_clover(const void* __restrict__ 
 #pragma unroll
         for (int f = 0; f < 12; ++f) pa[f] = sh[f * kWilsonSites + t];
 #pragma unroll
-        for (int f = 0; f < 12; ++f) acc[f] = {fmadd(diag, pa[f].re, acc[f].re), fmadd(diag, pa[f].im, acc[f].im)};
+        for (int f = 0; f < 12; ++f) acc[f] = cscale_add(acc[f], diag, pa[f]);
         if (use_clover) herm_mul_add<LF>(acc, pa, clov, cscale, site, V);
         hop_load_near<NEAR, 1, false, LF, VF, LR>(pa, ua, sh, in, in_scale, U, V, site, nb[2], base, vo, last);
         hop_apply<1, false>(acc, pa, ua);
@@ -305,7 +305,7 @@ __device__ __forceinline__ void eo_self_terms(cpx<R> acc[12], const void* __rest
             for (int f = 0; f < 12; ++f) acc[f] = p[f];
         } else {
 #pragma unroll
-            for (int f = 0; f < 12; ++f) acc[f] = {diag * p[f].re, diag * p[f].im};
+            for (int f = 0; f < 12; ++f) acc[f] = cscale_add(cpx<R>{R(0), R(0)}, diag, p[f]);
             if (use_clover) herm_mul_add<LF>(acc, p, clov, cscale, ie, V);
         }
     }
@@ -574,8 +574,7 @@ __global__ __launch_bounds__(SELF == 2 ? 768 : 640, sizeof(typename FineT<LF>::R
                     B::get(wv, b + (8 + CHI) * B::n, l);
 #pragma unroll
                     for (int f = 0; f < 6; ++f)
-                        acc[f] = cadd(cpx<R>{fmadd(diag, p[f].re, acc[f].re), fmadd(diag, p[f].im, acc[f].im)},
-                                      wv[f / 3][f % 3]);
+                        acc[f] = cadd(cscale_add(acc[f], diag, p[f]), wv[f / 3][f % 3]);
                 }
             };
             auto add = [&](auto mu_, auto back_) {

@@ -36,6 +36,13 @@ template <typename R>
 __device__ __forceinline__ cpx<R> cfmac(cpx<R> t, cpx<R> a, cpx<R> b) {
     return {t.re + fmadd(a.re, b.re, a.im * b.im), t.im + fmadd(a.re, b.im, -(a.im * b.re))};
 }
+// t + s a for a real s, rounded once per part in every kernel (left to the
+// compiler, s a into a zero t would be joined with the sum that follows it in
+// some kernels and not in others)
+template <typename R>
+__device__ __forceinline__ cpx<R> cscale_add(cpx<R> t, R s, cpx<R> a) {
+    return {fmadd(s, a.re, t.re), fmadd(s, a.im, t.im)};
+}
 template <typename R> __device__ __forceinline__ cpx<R> ci(cpx<R> a) { return {-a.im, a.re}; }   // i a
 template <typename R> __device__ __forceinline__ cpx<R> cmi(cpx<R> a) { return {a.im, -a.re}; }  // -i a
 template <typename R> __device__ __forceinline__ cpx<R> cneg(cpx<R> a) { return {-a.re, -a.im}; }

@@ -226,3 +226,48 @@ def test_direction_waves_at_the_edges(dims, nrhs, storage, link_reals):
             bound = tol if storage in ('c128', 'c64') else 8 * (2.0 ** -11 if storage == 'h16' else 2.0 ** -8)
             assert rel_err(host(ys[k]), S.apply(P[k][:V // 2].reshape(V // 2, 12)).reshape(V // 2, 4, 3)) <= bound
             assert torch.equal(ys[k], op.schur(pe[k].contiguous()))
+
+
+@pytest.mark.parametrize('storage,link_reals,csw', [('c128', 18, 1.0), ('c64', 18, 1.0), ('c64', 12, 1.0),
+                                                    ('h16', 18, 1.0), ('b16', 12, 1.0), ('c64', 18, 0.0)])
+@pytest.mark.parametrize('dims', [
+    (18, 10, 14, 28),   # 70560 sites, 35280 of a parity: neither a multiple of 256; an x-y plane that does not divide 256
+    (16, 8, 17, 17),    # 36992 sites, whole x-y planes per work-group, the last one half empty
+])
+def test_single_member_and_batch_forms_agree_on_large_lattices(dims, storage, link_reals, csw):
+    """Above 32768 sites a single application runs one thread per site and a
+    batch of four one wave per hop direction: the two agree to the bit, and the
+    single one with the oracle on the stored links and clover term (FP32 sums of
+    a hundred products: 1e-5; FP64 1e-12), whole lattice and every red-black
+    piece."""
+    from oracle import evenodd
+    from paper_1612_07873_amd import FineOp
+    V, m0, nrhs = lattice.volume(dims), -0.2, 4
+    U = synth.gauge_field(dims, 0.4, 5)
+    cdt = torch.complex128 if storage == 'c128' else torch.complex64
+    tol = 1e-12 if storage == 'c128' else 1e-5
+    op = FineOp(dims, dev(U), m0, csw, True, storage, link_reals=link_reals)
+    A, Us = host(op.clover()) if csw else None, host(op.links())
+    P = synth.gaussian((V, 4, 3), 30, 2)
+    one = dev(P, cdt)
+    batch = torch.stack([dev(synth.gaussian((V, 4, 3), 30 + k, 2), cdt) for k in range(nrhs)])
+    forms = {'apply': (op.apply, one, batch)}
+    if all(d % 2 == 0 for d in dims):
+        h = V // 2
+        forms['schur'] = (op.schur, one[:h].contiguous(), batch[:, :h].contiguous())
+        forms['schur_source'] = (op.schur_source, one, batch)
+        forms['schur_reconstruct'] = (op.schur_reconstruct, (one[h:].contiguous(), one), (batch[:, h:].contiguous(), batch))
+        S = evenodd.fine_schur(Us, A, m0, dims)
+        # C^-1 is rounded to the storage a second time: the 16-bit bound of the red-black tests
+        bound = tol if storage in ('c128', 'c64') else 8 * (2.0 ** -11 if storage == 'h16' else 2.0 ** -8)
+    differ = []
+    for name, (f, x, xs) in forms.items():
+        y = f(*x) if isinstance(x, tuple) else f(x)
+        ys = f(*xs) if isinstance(xs, tuple) else f(xs)
+        if not torch.equal(ys[0], y):
+            differ.append((name, int((torch.view_as_real(ys[0]) != torch.view_as_real(y)).sum())))
+        if name == 'apply':
+            assert rel_err(host(y), wilson.apply_wilson_clover(P, Us, A, m0, dims)) <= tol
+        elif name == 'schur':
+            assert rel_err(host(y), S.apply(P[:h].reshape(h, 12)).reshape(h, 4, 3)) <= bound
+    assert not differ, differ
