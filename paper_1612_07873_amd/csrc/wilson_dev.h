@@ -107,14 +107,27 @@ __device__ __forceinline__ void load_link_at(cpx<R> u[9], const void* __restrict
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             const int k = (j + 1) % 3, l = (j + 2) % 3;
-            // conj(a_k b_l - a_l b_k)
-            R re = u[k].re * u[3 + l].re, im = u[k].re * u[3 + l].im;
-            re = fmadd(-u[k].im, u[3 + l].im, re);
-            re = fmadd(-u[l].re, u[3 + k].re, re);
-            re = fmadd(u[l].im, u[3 + k].im, re);
-            im = fmadd(u[k].im, u[3 + l].re, im);
-            im = fmadd(-u[l].re, u[3 + k].im, im);
-            im = fmadd(-u[l].im, u[3 + k].re, im);
+            // conj(a_k b_l - a_l b_k).  16-bit links: the two products side by
+            // side, the shorter chain; FP32 links: one chain of multiply-adds, two
+            // operations fewer (16^3x32, source / Schur operator: FP16 18.8 / 24.4
+            // us against 20.1 / 24.9 us as a chain, FP32 21.3 / 28.5 us against
+            // 21.0 / 28.1 us).
+            R re, im;
+            if constexpr (is16f<LF>()) {
+                re = fmadd(u[k].re, u[3 + l].re, -(u[k].im * u[3 + l].im)) -
+                     fmadd(u[l].re, u[3 + k].re, -(u[l].im * u[3 + k].im));
+                im = fmadd(u[k].re, u[3 + l].im, u[k].im * u[3 + l].re) -
+                     fmadd(u[l].re, u[3 + k].im, u[l].im * u[3 + k].re);
+            } else {
+                re = u[k].re * u[3 + l].re;
+                im = u[k].re * u[3 + l].im;
+                re = fmadd(-u[k].im, u[3 + l].im, re);
+                re = fmadd(-u[l].re, u[3 + k].re, re);
+                re = fmadd(u[l].im, u[3 + k].im, re);
+                im = fmadd(u[k].im, u[3 + l].re, im);
+                im = fmadd(-u[l].re, u[3 + k].im, im);
+                im = fmadd(-u[l].im, u[3 + k].re, im);
+            }
             u[6 + j] = cpx<R>{sg * re, -sg * im};
         }
     }
