@@ -236,6 +236,15 @@ __device__ __forceinline__ void ld_run(Raw<ST, n>& v, const ST* row, int c0, int
     }
 }
 
+// Orders a wave's own LDS accesses in the program: the hardware completes them
+// in order, the fences (no instructions at this scope) keep the compiler from
+// moving them past each other.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Restriction: S(m, n) = sum over the rows r of an (aggregate, chirality) of
 // basis(r, m) field(r, n), m = (k, re/im), n = (member, re/im); the coarse
 // component is then S(k re, j re) + S(k im, j im) + i [S(k re, j im) - S(k im, j re)].
@@ -315,7 +324,7 @@ __global__ __launch_bounds__(64 * kRestrictWaves, T <= 3 && NT <= 2 && sizeof(R)
             for (int u = 0; u < U; ++u)
                 if (16 * c + 4 * u + g >= rows) d[u].zero();
         }
-        __builtin_amdgcn_wave_barrier();   // the wave's LDS accesses complete in order
+        wave_lds_sync();   // its lanes read what others wrote
         V4 acc[T][NT];
 #pragma unroll
         for (int r = 0; r < T; ++r)
@@ -331,7 +340,7 @@ __global__ __launch_bounds__(64 * kRestrictWaves, T <= 3 && NT <= 2 && sizeof(R)
 #pragma unroll
                 for (int t = 0; t < NT; ++t) acc[r][t] = Mm<R>::mac(d[u].template get<R>(r), b[t], acc[r][t]);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();   // the next chunk overwrites it
 #pragma unroll
         for (int r = 0; r < T; ++r)
 #pragma unroll
