@@ -223,16 +223,21 @@ __device__ __forceinline__ void ld_cols(Raw<ST, T>& v, const ST* row, int i, int
         for (int t = 0; t < T; ++t) v.v[t] = __builtin_nontemporal_load(row + (FULL ? T * i + t : min(T * i + t, cols - 1)));
     }
 }
-// n (even) consecutive reals from column c0 on; zero past the last column
-template <bool FULL, typename ST, int n>
-__device__ __forceinline__ void ld_run(Raw<ST, n>& v, const ST* row, int c0, int cols) {
-    if constexpr (sizeof(ST) == 2) {
-        const uint32_t* w = reinterpret_cast<const uint32_t*>(row + c0);
+// The columns of a basis row that lane group g of 4 holds in the prolongation:
+// runs of L consecutive ones, run q at 4 L q + L g.  Zero past the last column.
+template <bool FULL, int L, typename ST, int n>
+__device__ __forceinline__ void ld_runs(Raw<ST, n>& v, const ST* row, int g, int cols) {
 #pragma unroll
-        for (int i = 0; i < n / 2; ++i) v.v[i] = FULL || c0 + 2 * i < cols ? w[i] : 0u;
-    } else {
+    for (int s = 0; s < n; s += L) {
+        const int c0 = 4 * s + L * g;
+        if constexpr (sizeof(ST) == 2) {
+            const uint32_t* w = reinterpret_cast<const uint32_t*>(row + c0);
 #pragma unroll
-        for (int i = 0; i < n; ++i) v.v[i] = FULL || c0 + i < cols ? row[c0 + i] : ST(0);
+            for (int i = 0; i < L / 2; ++i) v.v[s / 2 + i] = FULL || c0 + 2 * i < cols ? w[i] : 0u;
+        } else {
+#pragma unroll
+            for (int i = 0; i < L; ++i) v.v[s + i] = FULL || c0 + i < cols ? row[c0 + i] : ST(0);
+        }
     }
 }
 
@@ -394,19 +399,27 @@ __global__ __launch_bounds__(64 * kRestrictWaves, T <= 3 && NT <= 2 && sizeof(R)
 // A work-group takes up to kProlongTiles tiles of 16 rows (grid dimension z
 // divides an aggregate's tiles evenly), whose places in a fine field it first
 // puts in LDS.  The coarse operand stays in registers while a wave walks its
-// tiles; lane group g (of 16 lanes) holds the KS columns g KS ... of its rows,
-// 48 contiguous bytes per lane at nvec 24, and the next tile's are loaded
-// while this one is multiplied.  Lanes of the two parts of a member exchange
-// halves, so that each stores whole complex numbers (16 bytes where the rows
-// of a chirality are even in number and `out` is so aligned: `wide`).
-// FULL: 2 nvec = 4 KS.
+// tiles; lane group g (of 16 lanes) holds KS columns of its rows in runs of L
+// (ld_runs), and the next tile's are loaded while this one is multiplied.  A
+// product of depth four takes one column of each lane group.  D neighbouring ones
+// are added up in one chain (D = 1: one chain each, the chains of a pair added),
+// these chains in order, then the runs: one chain over all columns had 1.6 times
+// the error at nvec 24 (prolong_t chooses D).  Lanes of the two parts of a
+// member exchange halves, so that each stores whole complex numbers (16 bytes
+// where the rows of a chirality are even in number and `out` is so aligned:
+// `wide`).  FULL: 2 nvec = 4 KS.
 template <typename R> constexpr int kProlongTiles = sizeof(R) == 4 ? 16 : 32;   // complex64 66 (32 tiles) -> 63 us, complex128 132 (32) against 147 (16)
 
-template <typename R, typename ST, int KS, int NT, bool FULL>
-__global__ __launch_bounds__(256) void k_prolong(cpx<R>* __restrict__ out, const ST* __restrict__ B,
-                                                 const cpx<R>* __restrict__ uc, const int* __restrict__ members,
-                                                 int dof, int nvec, int bsites, int64_t V, int64_t Vc, int nrhs,
-                                                 int wide) {
+// Waves per SIMD, by the bytes of coarse operand a lane holds.  (Two or more
+// also keep the accumulators where the vector unit can add them.)
+constexpr int prolong_waves(int NT, int bytes) {
+    return NT <= 2 && bytes <= 128 ? (NT == 1 ? 4 : 3) : bytes <= 256 ? 2 : 1;
+}
+
+template <typename R, typename ST, int KS, int L, int D, int NT, bool FULL>
+__global__ __launch_bounds__(256, prolong_waves(NT, KS * NT * (int)sizeof(R))) void k_prolong(
+    cpx<R>* __restrict__ out, const ST* __restrict__ B, const cpx<R>* __restrict__ uc, const int* __restrict__ members,
+    int dof, int nvec, int bsites, int64_t V, int64_t Vc, int nrhs, int wide) {
     using V4 = typename Mm<R>::V4;
     __shared__ int64_t at[16 * kProlongTiles<R>];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
@@ -434,7 +447,7 @@ __global__ __launch_bounds__(256) void k_prolong(cpx<R>* __restrict__ out, const
         const cpx<R>* c = uc + ((int64_t)j * Vc + xc) * cols + chi * nvec;
 #pragma unroll
         for (int s = 0; s < KS; s += 2) {
-            const int e = g * KS + s;
+            const int e = 4 * (s - s % L) + L * g + s % L;
             cpx<R> v = {0, 0};
             if (FULL || e < cols) v = c[e >> 1];
             b[s][t] = odd ? v.im : v.re;
@@ -445,19 +458,27 @@ __global__ __launch_bounds__(256) void k_prolong(cpx<R>* __restrict__ out, const
     auto load = [&](Raw<ST, KS>& a, int tile) {
         int64_t x = at[16 * tile + i16];
         if (x < 0) x = at[16 * tile];   // rows past the end: the tile's first row, not stored
-        ld_run<FULL>(a, B + x * cols, g * KS, cols);
+        ld_runs<FULL, L>(a, B + x * cols, g, cols);
     };
     const int n = t1 - t0;
     auto step = [&](Raw<ST, KS>& a, int tile) {
         // this lane's two rows: elements 0 and 1 (even lanes) or 2 and 3 (odd lanes)
         const int64_t o0 = at[16 * tile + Mm<R>::row(g, 2 * odd)], o1 = at[16 * tile + Mm<R>::row(g, 2 * odd + 1)];
-        V4 acc[NT];
+        V4 acc[NT], run[NT];
 #pragma unroll
-        for (int t = 0; t < NT; ++t) acc[t] = V4{0, 0, 0, 0};
+        for (int s = 0; s < KS; s += 2) {
 #pragma unroll
-        for (int s = 0; s < KS; ++s)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] = Mm<R>::mac(a.template get<R>(s), b[s][t], acc[t]);
+            for (int t = 0; t < NT; ++t) {
+                const V4 zero = {0, 0, 0, 0};
+                V4 c = Mm<R>::mac(a.template get<R>(s), b[s][t], D == 4 && s % 4 ? run[t] : zero);
+                V4 d = Mm<R>::mac(a.template get<R>(s + 1), b[s + 1][t], D == 1 ? zero : c);
+                if constexpr (D == 1) d = c + d;
+                run[t] = D == 4 || s % L == 0 ? d : run[t] + d;
+                if ((s + 2) % L == 0) acc[t] = s >= L ? acc[t] + run[t] : run[t];
+                if (sizeof(R) == 8) __builtin_amdgcn_sched_barrier(0);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // else more products are started than there are registers for
+        }
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const R x0 = odd ? acc[t][0] : acc[t][2], x1 = odd ? acc[t][1] : acc[t][3];
@@ -478,7 +499,7 @@ __global__ __launch_bounds__(256) void k_prolong(cpx<R>* __restrict__ out, const
     // NB tiles in flight, one included; whole rounds first, whose loads are
     // unconditional (a load under a condition makes the next wait one for all
     // loads before it)
-    constexpr int NB = 2;
+    constexpr int NB = KS * NT * sizeof(R) <= 256 ? 2 : 1;
     Raw<ST, KS> a[NB];
 #pragma unroll
     for (int k = 0; k < NB; ++k)
@@ -851,7 +872,7 @@ extern "C" qmg_status qmg_transfer_export(qmg_transfer t, void* basis, void* str
 }
 
 namespace qmg {
-template <typename R, typename ST, int KS, int NT>
+template <typename R, typename ST, int KS, int L, int D, int NT>
 static void prolong_nt(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
     const int tiles = (t->bsites * (t->dof / 2) + 15) / 16;
     // work-groups per (aggregate, chirality): at most kProlongTiles tiles each,
@@ -863,30 +884,45 @@ static void prolong_nt(qmg_transfer t, const void* B, const void* in, void* out,
     // the rows of a pair share a site, and pairs start at even components
     const int wide = (t->dof / 2) % 2 == 0 && (uintptr_t)out % 16 == 0;
     if (2 * t->nvec == 4 * KS)
-        hipLaunchKernelGGL((k_prolong<R, ST, KS, NT, true>), grid, dim3(256), 0, s, (cpx<R>*)out, (const ST*)B,
+        hipLaunchKernelGGL((k_prolong<R, ST, KS, L, D, NT, true>), grid, dim3(256), 0, s, (cpx<R>*)out, (const ST*)B,
                            (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, t->V, t->Vc, nb, wide);
     else
-        hipLaunchKernelGGL((k_prolong<R, ST, KS, NT, false>), grid, dim3(256), 0, s, (cpx<R>*)out, (const ST*)B,
+        hipLaunchKernelGGL((k_prolong<R, ST, KS, L, D, NT, false>), grid, dim3(256), 0, s, (cpx<R>*)out, (const ST*)B,
                            (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, t->V, t->Vc, nb, wide);
 }
 
-template <typename R, typename ST, int KS>
-static void prolong_ks(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+// The prolongation for one shape of its sums (KS columns per lane group in runs
+// of L, D).
+template <typename R, typename ST, int KS, int L, int D>
+static void prolong_form(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
     // column tiles per wave: the coarse operand takes KS x NT registers
-    if (nb <= 8) return prolong_nt<R, ST, KS, 1>(t, B, in, out, nb, s);
-    if constexpr (KS * sizeof(R) <= 64)
-        if (nb > 16) return prolong_nt<R, ST, KS, 4>(t, B, in, out, nb, s);
-    prolong_nt<R, ST, KS, 2>(t, B, in, out, nb, s);
+    if (nb <= 8) return prolong_nt<R, ST, KS, L, D, 1>(t, B, in, out, nb, s);
+    if constexpr (KS * sizeof(R) <= (D > 1 ? 64 : 32))
+        if (nb > 16) return prolong_nt<R, ST, KS, L, D, 4>(t, B, in, out, nb, s);
+    prolong_nt<R, ST, KS, L, D, 2>(t, B, in, out, nb, s);
 }
 
+// The shape of the sums is a function of the number of vectors and of the
+// storage alone.  A run is 16 bytes of a lane group's row where its columns
+// divide so (FP16: from 25 vectors on).  D, the products in one chain, is as
+// large (faster, fewer registers) as leaves the error no larger than that of one
+// chain per two entries (FP32; FP16 up to four, FP64 one) and these chains added
+// in order.  The squared error of that order, in units of one rounding of the
+// result, and of two and one product: FP32 nvec 6 4.2, 4.5 and 4.0; 8 4.8, 5.5
+// and 4.5; 10 5.3, 5.9 and 5.2; 12 5.8 and 5.8; 24 8.9 and 7.2; 32 10.9 and 7.8.
 template <typename R, typename ST>
 static qmg_status prolong_t(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
     const int nv = t->nvec;
-    if (nv <= 8) prolong_ks<R, ST, 4>(t, B, in, out, nb, s);
-    else if (nv <= 16) prolong_ks<R, ST, 8>(t, B, in, out, nb, s);
-    else if (nv <= 24) prolong_ks<R, ST, 12>(t, B, in, out, nb, s);
-    else if (nv <= 32) prolong_ks<R, ST, 16>(t, B, in, out, nb, s);
-    else prolong_ks<R, ST, 32>(t, B, in, out, nb, s);
+    constexpr bool f64 = sizeof(ST) == 8;
+    constexpr int L = f64 ? 2 : 4, LW = sizeof(ST) == 2 ? 8 : L;
+    if (!f64 && nv <= 2) prolong_form<R, ST, 4, L, f64 ? 2 : 4>(t, B, in, out, nb, s);
+    else if (f64 ? nv >= 2 && nv <= 5 : nv == 6 || nv == 8) prolong_form<R, ST, 4, L, 1>(t, B, in, out, nb, s);
+    else if (nv <= 8) prolong_form<R, ST, 4, L, 2>(t, B, in, out, nb, s);
+    else if (!f64 && nv == 10) prolong_form<R, ST, 8, L, f64 ? 2 : 1>(t, B, in, out, nb, s);
+    else if (nv <= 16) prolong_form<R, ST, 8, L, 2>(t, B, in, out, nb, s);
+    else if (nv <= 24) prolong_form<R, ST, 12, L, 2>(t, B, in, out, nb, s);
+    else if (nv <= 32) prolong_form<R, ST, 16, LW, 2>(t, B, in, out, nb, s);
+    else prolong_form<R, ST, 32, LW, 2>(t, B, in, out, nb, s);
     QMG_LAUNCH_CHECK();
     return QMG_OK;
 }
