@@ -11,8 +11,9 @@
 // Apply, for all members of a batch together:
 //   prolong  (P u)(x)_f = sum_k V(x)_{f,k} u(xc(x))_{chi(f)*Nvec + k}
 //   restrict (R psi)(xc)_{chi*Nvec + k} = sum_{x in xc, chi(f) = chi} conj(V(x)_{f,k}) psi(x)_f
-// both as dense products per (aggregate, chirality) on the matrix cores, every
-// sum in a fixed order: no atomics, bitwise repeatable.
+// both as dense products per (aggregate, chirality), on the matrix cores or for
+// few members on the vector unit, every sum in one fixed order: no atomics,
+// bitwise repeatable, and a member of a batch equals the single call bitwise.
 // The basis is kept as [V][dof][Nvec] (row f of site x holds the Nvec
 // coefficients of its chirality) in the storage precision, plus an FP64 copy
 // for the Galerkin build.  The 16-bit storage keeps each complex entry as an
@@ -22,6 +23,7 @@
 #include "handles.h"
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 namespace qmg {
@@ -140,10 +142,12 @@ __global__ void k_to_h16(uint32_t* __restrict__ o, const double2* __restrict__ i
 // columns and the basis is read once for up to 32 members.  The bound is the
 // basis stream: complex64, 16^3x32, nvec 24, twelve members, 302 MB of basis
 // and 151 MB of fields.  One kernel per member (each re-reading the basis)
-// took 559 us (restriction) and 752 us (prolongation); these take 108 and 117.
+// took 524 us (restriction) and 673 us (prolongation); these take 83 and 113
+// (one call repeated; in turn, as a solve makes them, 108 and 108, the bytes moved
+// 1.00 and 1.10 times these).
 // Every column of a product is summed in the same order whatever the number of
-// members, so with a complex64 basis a member of a batch equals the single call
-// bitwise.
+// members, and the forms for few members below keep that order, so a member of
+// a batch equals the single call bitwise with every storage of the basis.
 template <typename R> struct Mm;
 template <> struct Mm<float> {
     typedef float V4 __attribute__((ext_vector_type(4)));
@@ -522,166 +526,282 @@ __global__ __launch_bounds__(256, prolong_waves(NT, KS * NT * (int)sizeof(R))) v
     }
 }
 
-// ------------------------------------------ one member, FP16 or FP64 basis
-// A single field does not fill the matrix cores (2 of 16 columns).  With an
-// FP16 basis (half the bytes) or in FP64 one thread per 16-byte chunk of the
-// basis is faster there: 16^3x32, nvec 24, both directions, FP16 65 us against
-// 85, FP64 230 against 248.  (With a complex64 basis 116 against 114: one form
-// for every number of members.)  BT: the stored entry, cpx<double> or a 32-bit
-// FP16 pair.
+// ----------------------------------------------------- on the vector unit
+// One field fills 2 of the matrix cores' 16 columns, and with few vectors
+// their tiles are mostly padding.  The same products on the vector unit, each
+// member reading the basis for itself.  A matrix product of depth four is a
+// chain of multiply-adds in the order of its depth, so these kernels form the
+// sums above term by term: a field's result does not depend on the form, and
+// the choice between them (transfer_prolong, transfer_restrict) is one of speed
+// alone.  Bound: the basis stream.  One member, 16^3x32, nvec 24, restriction and
+// prolongation: FP32 51 and 55 us (302 MB each; on the matrix cores 57 and 62),
+// FP16 29 and 31 (48 and 37), FP64 103 and 118 us (122 and 127).  32^3x64: FP32
+// 756 and 1020 us, FP16 426 and 562 us (2.4 GB each).
+// BT: the stored entry, cpx<R> or a 32-bit FP16 pair.
 template <typename R> __device__ __forceinline__ cpx<R> bval(const cpx<R>& b) { return b; }
 template <typename R> __device__ __forceinline__ cpx<R> bval(const uint32_t& w) { return dec_pair<FMT_H16>(w); }
+__device__ __forceinline__ float fma_r(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_r(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// CPC consecutive basis entries, read once per application: non-temporal
-// loads, so the basis stream does not push the fine vector being restricted
-// out of the caches (the prolongation, which reads the small coarse vector,
-// was slower with them and keeps plain loads).
-template <typename BT, int CPC>
-__device__ __forceinline__ void ld_basis(BT (&b)[CPC], const BT* p) {
-    constexpr int words = (int)sizeof(BT) * CPC / 4;
+// P consecutive entries in one load.  NT: non-temporal, so that the basis
+// stream does not push the fine vector being restricted out of the caches (the
+// prolongation, which reads the small coarse vector, is slower with them).
+template <bool NT, int P, typename BT>
+__device__ __forceinline__ void ld_entries(BT* b, const BT* p) {
+    constexpr int words = (int)sizeof(BT) * P / 4;
     if constexpr (words == 1) {
-        const int v = __builtin_nontemporal_load(reinterpret_cast<const int*>(p));
+        const int* w = reinterpret_cast<const int*>(p);
+        const int v = NT ? __builtin_nontemporal_load(w) : *w;
         __builtin_memcpy(b, &v, 4);
     } else {
+        static_assert(words == 2 || words == 4, "4, 8 or 16 bytes");
         typedef int vec __attribute__((ext_vector_type(words)));
-        static_assert(words == 2 || words == 4, "basis chunks of 4, 8 or 16 bytes");
-        const vec v = __builtin_nontemporal_load(reinterpret_cast<const vec*>(p));
+        const vec* w = reinterpret_cast<const vec*>(p);
+        const vec v = NT ? __builtin_nontemporal_load(w) : *w;
         __builtin_memcpy(b, &v, sizeof(v));
     }
 }
 
-// Prolongation: one thread per 16-byte chunk of the basis ([x][f][k] row
-// major, so a wave reads one contiguous span).  A work-group covers RPT
-// consecutive spans of rows_per_wg rows; each thread issues its RPT chunk
-// loads before any arithmetic so that enough bytes are in flight to cover
-// HBM latency.  The `cpr` chunks of a row (x, f) are then summed in LDS in a
-// fixed order, one thread per row.
-template <typename R, typename BT, int CPC, int RPT>
-__global__ __launch_bounds__(256) void k_prolong_one(cpx<R>* __restrict__ out, const BT* __restrict__ B,
-                                                 const cpx<R>* __restrict__ uc, const int* __restrict__ owner,
-                                                 int64_t V, int dof, int nvec, int rows_per_wg) {
-    constexpr int cpc = CPC;
-    __shared__ cpx<R> part[RPT][256];
-    const int cpr = nvec / cpc;                    // chunks per row
-    const int t = threadIdx.x;
-    const int lr = t / cpr, kc = t - (t / cpr) * cpr;
-    const int64_t rows = V * dof;
-    const int64_t base = (int64_t)blockIdx.x * rows_per_wg * RPT;
-    BT b[RPT][cpc];
+// The sum of a run for one row: entry h of lane group g at H g + h, GN groups.
+template <int H, int GN, int D, typename R, typename BT>
+__device__ __forceinline__ cpx<R> run_sum(const BT* b, const cpx<R>* u) {
+    cpx<R> sum = {0, 0};
+    R x1 = 0, y1 = 0;
 #pragma unroll
-    for (int j = 0; j < RPT; ++j) {
-        const int64_t row = base + (int64_t)j * rows_per_wg + lr;
-        if (lr < rows_per_wg && row < rows) {
+    for (int h = 0; h < H; ++h) {
+        // the entries' real parts, then their imaginary ones: a chain per product, both in one, or on from the entry before
+        R x = D == 4 ? x1 : R(0), y = D == 4 ? y1 : R(0);
 #pragma unroll
-            for (int q = 0; q < cpc; ++q) b[j][q] = B[row * nvec + kc * cpc + q];
+        for (int g = 0; g < GN; ++g) {
+            const cpx<R> w = bval<R>(b[H * g + h]), v = u[H * g + h];
+            x = fma_r(w.re, v.re, x);
+            y = fma_r(w.re, v.im, y);
+        }
+        x1 = D == 1 ? R(0) : x;
+        y1 = D == 1 ? R(0) : y;
+#pragma unroll
+        for (int g = 0; g < GN; ++g) {
+            const cpx<R> w = bval<R>(b[H * g + h]), v = u[H * g + h];
+            x1 = fma_r(w.im, -v.im, x1);
+            y1 = fma_r(w.im, v.re, y1);
+        }
+        if (D == 1) {
+            x1 = x + x1;
+            y1 = y + y1;
+        }
+        sum = h && D != 4 ? cpx<R>{sum.re + x1, sum.im + y1} : cpx<R>{x1, y1};
+    }
+    return sum;
+}
+
+// Prolongation: a lane takes a run of 4 L columns (2 L entries), keeps its part
+// of the coarse vector and walks the rows of a slab of an (aggregate, chirality),
+// one slab per wave; the lanes of a row add their runs in order.  The next row's
+// entries are in flight while one is multiplied.  Loads of P entries, which
+// divides nvec; FULL: 2 L does.
+constexpr int kProlongRows = 256;   // most rows of a slab
+
+template <typename R, typename BT, int L, int D, int P, bool FULL>
+__global__ __launch_bounds__(256) void k_prolong_vec(cpx<R>* __restrict__ out, const BT* __restrict__ B,
+                                                     const cpx<R>* __restrict__ uc, const int* __restrict__ members,
+                                                     int dof, int nvec, int bsites, int64_t V, int64_t Vc, int slabs) {
+    constexpr int E = 2 * L;
+    __shared__ int64_t places[4 * kProlongRows];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int64_t unit = 4 * (int64_t)blockIdx.x + w, agg = unit / slabs;
+    if (agg >= 2 * Vc) return;   // the whole wave; no barrier below
+    const int slab = (int)(unit - agg * slabs);
+    const int64_t xc = agg >> 1;
+    const int chi = (int)(agg & 1);
+    const int half = dof >> 1, rows = bsites * half;
+    const int r0 = (int)((int64_t)rows * slab / slabs), n = (int)((int64_t)rows * (slab + 1) / slabs) - r0;
+    int64_t* at = places + w * kProlongRows;
+    for (int e = l; e < n; e += 64) {
+        const int site = (r0 + e) / half;
+        at[e] = (int64_t)members[xc * bsites + site] * dof + chi * half + (r0 + e - site * half);
+    }
+    const int gpr = (nvec + E - 1) / E;        // runs of a row, lanes next to each other
+    const int rpw = 64 / gpr;                  // rows of a turn
+    const int lr = l / gpr, q = l - lr * gpr;
+    const bool mine = lr < rpw;
+    cpx<R> u[E];
+    {
+        const cpx<R>* c = uc + ((int64_t)blockIdx.y * Vc + xc) * 2 * nvec + chi * nvec;
+#pragma unroll
+        for (int i = 0; i < E; ++i) u[i] = FULL || E * q + i < nvec ? c[E * q + i] : cpx<R>{0, 0};
+    }
+    out += (int64_t)blockIdx.y * V * dof;
+    wave_lds_sync();
+    // a row past the end is the last one again, not stored
+    auto load = [&](BT (&b)[E], int r) {
+        const BT* p = B + at[mine && r < n ? r : n - 1] * nvec;
+#pragma unroll
+        for (int i = 0; i < E; i += P) {
+            const bool ok = FULL || E * q + i < nvec;
+            ld_entries<false, P>(b + i, p + (ok ? E * q + i : 0));
+            if (!ok)
+#pragma unroll
+                for (int k = 0; k < P; ++k) b[i + k] = BT{};
+        }
+    };
+    auto row = [&](const BT (&b)[E], int r) {
+        const cpx<R> v = run_sum<L / 2, 4, D, R>(b, u);
+        cpx<R> sum = v;
+        for (int k = 1; k < gpr; ++k) {
+            sum.re += __shfl(v.re, (l + k) & 63, 64);
+            sum.im += __shfl(v.im, (l + k) & 63, 64);
+        }
+        if (mine && q == 0 && r < n) out[at[r]] = sum;
+    };
+    BT b0[E], b1[E];
+    load(b0, lr);
+    for (int r = lr, k = 0; k < n; r += 2 * rpw, k += 2 * rpw) {   // every lane takes the same number of turns
+        load(b1, r + rpw);
+        row(b0, r);
+        load(b0, r + 2 * rpw);
+        row(b1, r + rpw);
+    }
+}
+
+// The same where nvec is at most L: a thread per row, in lattice order, four
+// rows of a thread in flight, the members one after another.
+template <typename R, typename BT, int L, int D, int P>
+__global__ __launch_bounds__(256) void k_prolong_few(cpx<R>* __restrict__ out, const BT* __restrict__ B,
+                                                     const cpx<R>* __restrict__ uc, const int* __restrict__ owner,
+                                                     int dof, int nvec, int64_t V, int64_t Vc, int nb) {
+    constexpr int U = 4;
+    const int64_t rows = V * dof, r0 = (int64_t)blockIdx.x * (256 * U) + threadIdx.x;
+    BT b[U][L];
+    int64_t c[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        const int64_t r = r0 + 256 * j < rows ? r0 + 256 * j : rows - 1;
+        const int64_t x = r / dof;
+        const int chi = (int)(r - x * dof) >= (dof >> 1);
+        c[j] = ((int64_t)owner[x] * 2 + chi) * nvec;
+#pragma unroll
+        for (int i = 0; i < L; i += P) {
+            const bool ok = i < nvec;   // P divides nvec
+            ld_entries<false, P>(&b[j][i], B + r * nvec + (ok ? i : 0));
+            if (!ok)
+#pragma unroll
+                for (int k = 0; k < P; ++k) b[j][i + k] = BT{};
         }
     }
+    for (int m = 0; m < nb; ++m, uc += Vc * 2 * nvec, out += rows) {
+        cpx<R> u[U][L];
 #pragma unroll
-    for (int j = 0; j < RPT; ++j) {
-        const int64_t row = base + (int64_t)j * rows_per_wg + lr;
-        R ar = 0, ai = 0;
-        if (lr < rows_per_wg && row < rows) {
-            const int64_t x = row / dof;
-            const int f = (int)(row - x * dof);
-            const int chi = f / (dof / 2);
-            const cpx<R>* u = uc + (int64_t)owner[x] * 2 * nvec + chi * nvec + kc * cpc;
+        for (int j = 0; j < U; ++j)
 #pragma unroll
-            for (int q = 0; q < cpc; ++q) {
-                const cpx<R> bq = bval<R>(b[j][q]);
-                cmac(ar, ai, bq.re, bq.im, u[q].re, u[q].im);
-            }
-        }
-        part[j][t] = cpx<R>{ar, ai};
-    }
-    __syncthreads();
-    for (int rr = t; rr < rows_per_wg * RPT; rr += 256) {
-        const int j = rr / rows_per_wg, r = rr - j * rows_per_wg;
-        const int64_t row = base + rr;
-        if (row < rows) {
-            R sr = 0, si = 0;
-            for (int q = 0; q < cpr; ++q) {
-                sr += part[j][r * cpr + q].re;
-                si += part[j][r * cpr + q].im;
-            }
-            out[row] = cpx<R>{sr, si};
+            for (int i = 0; i < L; ++i) u[j][i] = i < nvec ? uc[c[j] + i] : cpx<R>{0, 0};
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const cpx<R> v = run_sum<L / 2, 2, D, R>(b[j], u[j]);
+            if (r0 + 256 * j < rows) out[r0 + 256 * j] = v;
         }
     }
 }
 
-// Restriction: one work-group per aggregate.  Thread (slice, q) owns chunk q
-// of the per-site basis block (dof x nvec, contiguous) and accumulates
-// conj(V) psi over the aggregate's sites slice, slice + S, ...; the S slices
-// and then the dof/2 rows of each chirality are summed in LDS in a fixed
-// order.  No atomics; bitwise repeatable.  With S = 1 the threads stride over
-// the chunks instead (blocks with more chunks than threads).
-template <typename R, typename BT, int CPC>
-__global__ __launch_bounds__(1024) void k_restrict_one(cpx<R>* __restrict__ out, const BT* __restrict__ B,
-                                                   const cpx<R>* __restrict__ in, const int* __restrict__ members,
-                                                   int dof, int nvec, int bsites, int S) {
-    constexpr int cpc = CPC;
+// Restriction: the sums of the chunks of 16 rows, one thread per chunk and P
+// vectors, go to LDS and are then added in the order of the waves of the form
+// above.  A work-group first puts the field and the place of every row it takes
+// into LDS (read by the threads where they use them, the lines of the fields and
+// of the site lists push those of the basis out of the L1: FP16 nvec 24, with
+// non-temporal loads, 42 us against 38).  It takes M (aggregate, chirality) units
+// where one has few chunks, and G chunks of a unit at a time where all do not fit
+// LDS (then a multiple of 8, and M = 1).  half_rec: ceil(2^32 / half); V dof fits
+// an int, bsites half^2 32 bits.
+template <typename R, typename BT, int P, bool NT>
+__global__ __launch_bounds__(256) void k_restrict_vec(cpx<R>* __restrict__ out, const BT* __restrict__ B,
+                                                      const cpx<R>* __restrict__ in, const int* __restrict__ members,
+                                                      int dof, int nvec, int bsites, int64_t V, int64_t Vc, int G, int M,
+                                                      uint32_t half_rec) {
+    struct Sum { R rr, ii, ri, ir; };
     extern __shared__ __align__(16) unsigned char smem[];
-    cpx<R>* acc_l = reinterpret_cast<cpx<R>*>(smem);   // [S][dof][nvec]
-    const int64_t xc = blockIdx.x;
-    const int* mem = members + xc * bsites;
-    const int cpr = nvec / cpc;
-    const int nchunk = dof * cpr;
-    const int slice = S > 1 ? (int)threadIdx.x / nchunk : 0;
-    const int q0 = S > 1 ? (int)threadIdx.x - slice * nchunk : (int)threadIdx.x;
-    const int qstep = S > 1 ? nchunk : (int)blockDim.x;
-    if (slice < S) {
-        cpx<R>* acc_s = acc_l + (int64_t)slice * dof * nvec;
-        for (int q = q0; q < nchunk; q += qstep) {
-            const int f = q / cpr, kc = q - (q / cpr) * cpr;
-            R ar[cpc], ai[cpc];
+    const int half = dof >> 1, rows = bsites * half, nch = (rows + 15) >> 4;
+    const bool one = nch <= G;                  // all chunks at once
+    Sum* part = reinterpret_cast<Sum*>(smem);   // [M][G][nvec]
+    Sum* tot = one ? part : part + G * nvec;    // the eight totals of a unit: in place, or carried
+    cpx<R>* fld = reinterpret_cast<cpx<R>*>(part + (M * G + (one ? 0 : 8)) * nvec);   // [M][G][17]
+    int* at = reinterpret_cast<int*>(fld + M * G * 17);                                // [M][G][17]
+    const int tid = threadIdx.x;
+    constexpr int T = 256;
+    int64_t unit0 = (int64_t)blockIdx.x * M;
+    if (M == 1) {                  // the two chiralities of an aggregate on one XCD, as above
+        int chi;
+        const int64_t xc = agg_of(blockIdx.x, Vc, chi);
+        unit0 = xc < 0 ? 2 * Vc : 2 * xc + chi;
+    }
+    if (unit0 >= 2 * Vc) return;   // the whole work-group
+    const int mu = (int)(2 * Vc - unit0 < M ? 2 * Vc - unit0 : M);
+    const int cpr = nvec / P;
+    const int nv = nch < 8 ? nch : 8;
+    in += (int64_t)blockIdx.y * V * dof;
+    for (int c0 = 0; c0 < nch; c0 += G) {
+        const int ng = nch - c0 < G ? nch - c0 : G;
+        for (int e0 = tid; e0 < mu * 16 * ng; e0 += T) {
+            const int m = e0 / (16 * ng), e = e0 - m * 16 * ng;
+            const int64_t unit = unit0 + m;
+            const int r = 16 * c0 + e < rows ? 16 * c0 + e : rows - 1;   // past the end the last row, not used
+            const int site = half == 1 ? r : (int)__umulhi((uint32_t)r, half_rec);
+            const int x = members[(unit >> 1) * bsites + site] * dof + (int)(unit & 1) * half + (r - site * half);
+            at[(m * G + (e >> 4)) * 17 + (e & 15)] = x;
+            fld[(m * G + (e >> 4)) * 17 + (e & 15)] = in[x];
+        }
+        __syncthreads();
+        const int items = ng * cpr;
+        for (int it = tid; it < mu * items; it += T) {
+            const int m = it / items, j = it - m * items;
+            const int cl = j / cpr, k0 = (j - cl * cpr) * P;
+            const int left = rows - 16 * (c0 + cl);      // rows of the chunk, 16 or more if whole
+            const int* a16 = at + (m * G + cl) * 17;
+            const cpx<R>* f16 = fld + (m * G + cl) * 17;
+            BT b[16][P];
 #pragma unroll
-            for (int c = 0; c < cpc; ++c) ar[c] = ai[c] = 0;
-            int b = slice;
-            for (; b + 3 * S < bsites; b += 4 * S) {
-                int64_t x[4];
-                cpx<R> v[4];
-                BT bb[4][cpc];
+            for (int r = 0; r < 16; ++r) ld_entries<NT, P>(b[r], B + (int64_t)a16[r] * nvec + k0);
+            Sum a[P];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    x[j] = mem[b + j * S];
-                    v[j] = in[x[j] * dof + f];
-                    ld_basis<BT, cpc>(bb[j], B + (x[j] * dof + f) * nvec + kc * cpc);
+            for (int i = 0; i < P; ++i) a[i] = Sum{0, 0, 0, 0};
+            __builtin_amdgcn_sched_barrier(0);   // all loads first
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const cpx<R> fv = r < left ? f16[r] : cpx<R>{0, 0};
+#pragma unroll
+                for (int i = 0; i < P; ++i) {
+                    const cpx<R> wv = bval<R>(r < left ? b[r][i] : BT{});
+                    a[i].rr = fma_r(wv.re, fv.re, a[i].rr);
+                    a[i].ii = fma_r(wv.im, fv.im, a[i].ii);
+                    a[i].ri = fma_r(wv.re, fv.im, a[i].ri);
+                    a[i].ir = fma_r(wv.im, fv.re, a[i].ir);
                 }
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int c = 0; c < cpc; ++c) {
-                        const cpx<R> bq = bval<R>(bb[j][c]);
-                        cmac_conj(ar[c], ai[c], bq.re, bq.im, v[j].re, v[j].im);
-                    }
+                if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // else every entry is decoded before the first product
             }
-            for (; b < bsites; b += S) {
-                const int64_t x = mem[b];
-                const cpx<R> v = in[x * dof + f];
-                BT bv[cpc];
-                ld_basis<BT, cpc>(bv, B + (x * dof + f) * nvec + kc * cpc);
 #pragma unroll
-                for (int c = 0; c < cpc; ++c) {
-                    const cpx<R> bq = bval<R>(bv[c]);
-                    cmac_conj(ar[c], ai[c], bq.re, bq.im, v.re, v.im);
+            for (int i = 0; i < P; ++i) part[(m * G + cl) * nvec + k0 + i] = a[i];
+        }
+        __syncthreads();
+        if (nch > 8) {
+            for (int o = tid; o < mu * 8 * nvec; o += T) {
+                const int m = o / (8 * nvec), vk = o - m * 8 * nvec;   // (class, vector)
+                Sum t = c0 ? tot[vk] : Sum{0, 0, 0, 0};
+                for (int e = vk; e < ng * nvec; e += 8 * nvec) {
+                    const Sum p = part[m * G * nvec + e];
+                    t = Sum{t.rr + p.rr, t.ii + p.ii, t.ri + p.ri, t.ir + p.ir};
                 }
+                tot[m * G * nvec + vk] = t;   // (M = 1 unless in place)
             }
-#pragma unroll
-            for (int c = 0; c < cpc; ++c) acc_s[f * nvec + kc * cpc + c] = cpx<R>{ar[c], ai[c]};
+            __syncthreads();
         }
     }
-    __syncthreads();
-    const int half = dof / 2;
-    const int64_t sstride = (int64_t)dof * nvec;
-    for (int n = threadIdx.x; n < 2 * nvec; n += blockDim.x) {
-        const int chi = n / nvec, k = n - chi * nvec;
-        R sr = 0, si = 0;
-        for (int ff = 0; ff < half; ++ff)
-            for (int sl = 0; sl < S; ++sl) {
-                const cpx<R> a = acc_l[sl * sstride + (chi * half + ff) * nvec + k];
-                sr += a.re;
-                si += a.im;
-            }
-        out[xc * 2 * nvec + n] = cpx<R>{sr, si};
+    for (int o = tid; o < mu * nvec; o += T) {
+        const int m = o / nvec, k = o - m * nvec;
+        R re = 0, im = 0;
+        for (int v = 0; v < nv; ++v) {
+            const Sum t = tot[(m * G + v) * nvec + k];
+            re += t.rr + t.ii;
+            im += t.ri - t.ir;
+        }
+        out[((int64_t)blockIdx.y * 2 * Vc + unit0 + m) * nvec + k] = cpx<R>{re, im};
     }
 }
 
@@ -891,15 +1011,44 @@ static void prolong_nt(qmg_transfer t, const void* B, const void* in, void* out,
                            (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, t->V, t->Vc, nb, wide);
 }
 
-// The prolongation for one shape of its sums (KS columns per lane group in runs
-// of L, D).
+template <typename R, typename BT, int L, int D, int P, bool FULL>
+static void prolong_vec_t(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+    const int gpr = (t->nvec + 2 * L - 1) / (2 * L), rows = t->bsites * (t->dof / 2);
+    const int per = 4 * (64 / gpr);   // rows of a slab: four turns of a wave
+    const int64_t slabs = (rows + per - 1) / per;
+    const dim3 grid((unsigned)((2 * t->Vc * slabs + 3) / 4), (unsigned)nb);
+    hipLaunchKernelGGL((k_prolong_vec<R, BT, L, D, P, FULL>), grid, dim3(256), 0, s, (cpx<R>*)out, (const BT*)B,
+                       (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, t->V, t->Vc, (int)slabs);
+}
+
+// The forms of the prolongation for one shape of its sums (KS columns per lane
+// group in runs of L, D).
 template <typename R, typename ST, int KS, int L, int D>
-static void prolong_form(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
-    // column tiles per wave: the coarse operand takes KS x NT registers
-    if (nb <= 8) return prolong_nt<R, ST, KS, L, D, 1>(t, B, in, out, nb, s);
-    if constexpr (KS * sizeof(R) <= (D > 1 ? 64 : 32))
-        if (nb > 16) return prolong_nt<R, ST, KS, L, D, 4>(t, B, in, out, nb, s);
-    prolong_nt<R, ST, KS, L, D, 2>(t, B, in, out, nb, s);
+static void prolong_form(qmg_transfer t, const void* B, const void* in, void* out, int nb, bool vec, hipStream_t s) {
+    if (!vec) {
+        // column tiles per wave: the coarse operand takes KS x NT registers
+        if (nb <= 8) return prolong_nt<R, ST, KS, L, D, 1>(t, B, in, out, nb, s);
+        if constexpr (KS * sizeof(R) <= (D > 1 ? 64 : 32))
+            if (nb > 16) return prolong_nt<R, ST, KS, L, D, 4>(t, B, in, out, nb, s);
+        return prolong_nt<R, ST, KS, L, D, 2>(t, B, in, out, nb, s);
+    }
+    using BT = std::conditional_t<sizeof(ST) == 2, uint32_t, cpx<R>>;
+    constexpr int most = 16 / sizeof(BT);   // entries of a 16-byte load
+    const int nv = t->nvec;
+    if constexpr (KS == 4)
+        if (nv <= L) {
+            auto go = [&](auto p) {
+                hipLaunchKernelGGL((k_prolong_few<R, BT, L, D, decltype(p)::value>),
+                                   dim3((unsigned)((t->V * t->dof + 1023) / 1024)), dim3(256), 0, s, (cpx<R>*)out, (const BT*)B,
+                                   (const cpx<R>*)in, t->owner, t->dof, nv, t->V, t->Vc, nb);
+            };
+            return nv == L ? go(std::integral_constant<int, most < L ? most : L>{}) : go(std::integral_constant<int, 1>{});
+        }
+    if (nv % (2 * L) == 0) return prolong_vec_t<R, BT, L, D, most, true>(t, B, in, out, nb, s);
+    if (nv % most == 0) return prolong_vec_t<R, BT, L, D, most, false>(t, B, in, out, nb, s);
+    if constexpr (most > 2)
+        if (nv % 2 == 0) return prolong_vec_t<R, BT, L, D, 2, false>(t, B, in, out, nb, s);
+    if constexpr (most > 1) prolong_vec_t<R, BT, L, D, 1, false>(t, B, in, out, nb, s);
 }
 
 // The shape of the sums is a function of the number of vectors and of the
@@ -911,18 +1060,18 @@ static void prolong_form(qmg_transfer t, const void* B, const void* in, void* ou
 // result, and of two and one product: FP32 nvec 6 4.2, 4.5 and 4.0; 8 4.8, 5.5
 // and 4.5; 10 5.3, 5.9 and 5.2; 12 5.8 and 5.8; 24 8.9 and 7.2; 32 10.9 and 7.8.
 template <typename R, typename ST>
-static qmg_status prolong_t(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+static qmg_status prolong_t(qmg_transfer t, const void* B, const void* in, void* out, int nb, bool vec, hipStream_t s) {
     const int nv = t->nvec;
     constexpr bool f64 = sizeof(ST) == 8;
     constexpr int L = f64 ? 2 : 4, LW = sizeof(ST) == 2 ? 8 : L;
-    if (!f64 && nv <= 2) prolong_form<R, ST, 4, L, f64 ? 2 : 4>(t, B, in, out, nb, s);
-    else if (f64 ? nv >= 2 && nv <= 5 : nv == 6 || nv == 8) prolong_form<R, ST, 4, L, 1>(t, B, in, out, nb, s);
-    else if (nv <= 8) prolong_form<R, ST, 4, L, 2>(t, B, in, out, nb, s);
-    else if (!f64 && nv == 10) prolong_form<R, ST, 8, L, f64 ? 2 : 1>(t, B, in, out, nb, s);
-    else if (nv <= 16) prolong_form<R, ST, 8, L, 2>(t, B, in, out, nb, s);
-    else if (nv <= 24) prolong_form<R, ST, 12, L, 2>(t, B, in, out, nb, s);
-    else if (nv <= 32) prolong_form<R, ST, 16, LW, 2>(t, B, in, out, nb, s);
-    else prolong_form<R, ST, 32, LW, 2>(t, B, in, out, nb, s);
+    if (!f64 && nv <= 2) prolong_form<R, ST, 4, L, f64 ? 2 : 4>(t, B, in, out, nb, vec, s);
+    else if (f64 ? nv >= 2 && nv <= 5 : nv == 6 || nv == 8) prolong_form<R, ST, 4, L, 1>(t, B, in, out, nb, vec, s);
+    else if (nv <= 8) prolong_form<R, ST, 4, L, 2>(t, B, in, out, nb, vec, s);
+    else if (!f64 && nv == 10) prolong_form<R, ST, 8, L, f64 ? 2 : 1>(t, B, in, out, nb, vec, s);
+    else if (nv <= 16) prolong_form<R, ST, 8, L, 2>(t, B, in, out, nb, vec, s);
+    else if (nv <= 24) prolong_form<R, ST, 12, L, 2>(t, B, in, out, nb, vec, s);
+    else if (nv <= 32) prolong_form<R, ST, 16, LW, 2>(t, B, in, out, nb, vec, s);
+    else prolong_form<R, ST, 32, LW, 2>(t, B, in, out, nb, vec, s);
     QMG_LAUNCH_CHECK();
     return QMG_OK;
 }
@@ -959,69 +1108,72 @@ static qmg_status restrict_t(qmg_transfer t, const void* B, const void* in, void
     return QMG_OK;
 }
 
-template <typename R, typename BT, int CPC>
-static qmg_status prolong_one(qmg_transfer t, const void* B, const void* in, void* out, hipStream_t s) {
-    constexpr int RPT = 4;
-    const int cpr = t->nvec / CPC;
-    const int rows_per_wg = 256 / cpr;
-    const int64_t rows = t->V * t->dof;
-    const int64_t per_wg = (int64_t)rows_per_wg * RPT;
-    const unsigned nblk = (unsigned)((rows + per_wg - 1) / per_wg);
-    hipLaunchKernelGGL((k_prolong_one<R, BT, CPC, RPT>), dim3(nblk), dim3(256), 0, s, (cpx<R>*)out, (const BT*)B,
-                       (const cpx<R>*)in, t->owner, t->V, t->dof, t->nvec, rows_per_wg);
+template <typename R, typename BT, int P, bool NT>
+static qmg_status restrict_vec_t(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+    const int half = t->dof / 2, nch = (t->bsites * half + 15) / 16, cpr = t->nvec / P;
+    const int sums = (int)(4 * sizeof(R)) * t->nvec, chunk = sums + 17 * (int)(sizeof(cpx<R>) + sizeof(int));   // LDS bytes
+    constexpr int budget = 32768;   // of LDS: five work-groups on a CU (four: 32^3x64, nvec 24, FP16 434 us against 426)
+    int G = nch, M = 1;
+    if (nch <= budget / chunk) {    // units that give every thread a chunk and P vectors
+        M = std::max(1, std::min(budget / chunk / nch, 256 / (nch * cpr)));
+    } else {
+        const int fit = std::max(8, (budget - 8 * sums) / chunk / 8 * 8);
+        const int passes = (nch + fit - 1) / fit;
+        G = ((nch + passes - 1) / passes + 7) / 8 * 8;
+    }
+    const size_t lds = (size_t)chunk * G * M + (G < nch ? 8 * sums : 0);
+    const dim3 grid((unsigned)(M == 1 ? agg_grid(t->Vc) : (2 * t->Vc + M - 1) / M), (unsigned)nb);
+    hipLaunchKernelGGL((k_restrict_vec<R, BT, P, NT>), grid, dim3(256), lds, s, (cpx<R>*)out, (const BT*)B,
+                       (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, t->V, t->Vc, G, M,
+                       (uint32_t)((0x100000000ull + half - 1) / half));
     QMG_LAUNCH_CHECK();
     return QMG_OK;
 }
-
-template <typename R, typename BT, int CPC>
-static qmg_status restrict_one(qmg_transfer t, const void* B, const void* in, void* out, hipStream_t s) {
-    const int nchunk = t->dof * (t->nvec / CPC);
-    const size_t lds1 = sizeof(cpx<R>) * t->dof * t->nvec;
-    // site slices per aggregate: as many as fit in 1024 threads and 64 KiB of
-    // LDS, at most 8 and at most the aggregate's sites
-    int S = 1024 / nchunk;
-    if (S > 8) S = 8;
-    if (S > t->bsites) S = t->bsites;
-    while (S > 1 && (size_t)S * lds1 > 65536) --S;
-    if (S < 1) S = 1;
-    int threads = S > 1 ? S * nchunk : nchunk;
-    threads = ((threads + 63) / 64) * 64;
-    if (threads > 1024) threads = 1024;
-    const size_t lds = lds1 * S;
-    if (lds > 65536)
-        QMG_HIP(hipFuncSetAttribute((const void*)k_restrict_one<R, BT, CPC>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)lds));
-    hipLaunchKernelGGL((k_restrict_one<R, BT, CPC>), dim3((unsigned)t->Vc), dim3(threads), lds, s, (cpx<R>*)out,
-                       (const BT*)B, (const cpx<R>*)in, t->members, t->dof, t->nvec, t->bsites, S);
-    QMG_LAUNCH_CHECK();
-    return QMG_OK;
+template <typename R, typename BT, int P>
+static qmg_status restrict_vec(qmg_transfer t, const void* B, const void* in, void* out, int nb, hipStream_t s) {
+    // Non-temporal loads of a basis that the last-level cache (256 MB) does not hold, where rows neither share a
+    // 64-byte sector nor are shorter than a cache line (one member, 4^4 blocks, with and without: 24^3x48 FP32 16
+    // vectors 159 and 181 us, 24 246 and 268; 16^3x32 FP32 32, 403 MB, 65 and 75).  Elsewhere the cache serves what
+    // it holds (8^3x16 FP32 24 16.1 and 12.4 us), and sectors that rows share would be fetched again (24^3x48 FP32
+    // 20, 160 bytes, 246 and 221 us, FP16 24, 96 bytes, 176 and 145).
+    const int row = t->nvec * (int)sizeof(BT);
+    return row >= 128 && row % 64 == 0 && t->V * t->dof * row > 320000000 ? restrict_vec_t<R, BT, P, true>(t, B, in, out, nb, s)
+                                                                          : restrict_vec_t<R, BT, P, false>(t, B, in, out, nb, s);
 }
 
-// one member in FP64 or with an FP16 basis (16-byte chunks of four pairs where
-// nvec allows, else 8 or 4 bytes); every other call goes to the dense products
-static bool one_member(qmg_transfer t, qmg_prec p, int nb) { return nb == 1 && (p == QMG_C128 || t->storage == QMG_H16); }
+// One member goes to the vector unit, as do up to four with so few vectors that a
+// thread holds a row: 16^3x32, FP32, prolongation on the vector unit / the matrix
+// cores in us, nvec 24: one member 55 / 62, two 104 / 68; nvec 4: two 17 / 25, four
+// 25 / 27, six 32 / 30.
+static bool prolong_on_vector_unit(bool f64, int nvec, int nb) { return nb == 1 || (nb <= 4 && nvec <= (f64 ? 2 : 4)); }
+// One member, and two with at most four vectors: restriction, FP32, nvec 24: one
+// member 51 / 57, two 99 / 53; nvec 4: two 26 / 29, three 37 / 29.
+// (The bounds: a row's place is kept as an int, and its site is found by a
+// product with ceil(2^32 / half), exact while rows x half stays below 2^32.)
+static bool restrict_on_vector_unit(const qmg_transfer_s* t, int nb) {
+    const int64_t half = t->dof / 2;
+    return (nb == 1 || (nb == 2 && t->nvec <= 4)) && t->V * t->dof <= INT32_MAX && t->bsites * half * half <= UINT32_MAX;
+}
 
 qmg_status transfer_prolong(qmg_transfer t, const void* in, void* out, qmg_prec p, int nb, hipStream_t s) {
-    if (one_member(t, p, nb)) {
-        if (p == QMG_C128) return prolong_one<double, cpx<double>, 1>(t, t->basis64, in, out, s);
-        if (t->nvec % 4 == 0) return prolong_one<float, uint32_t, 4>(t, t->basis, in, out, s);
-        if (t->nvec % 2 == 0) return prolong_one<float, uint32_t, 2>(t, t->basis, in, out, s);
-        return prolong_one<float, uint32_t, 1>(t, t->basis, in, out, s);
-    }
-    if (p == QMG_C128) return prolong_t<double, double>(t, t->basis64, in, out, nb, s);
-    if (t->storage == QMG_H16) return prolong_t<float, _Float16>(t, t->basis, in, out, nb, s);
-    return prolong_t<float, float>(t, t->basis, in, out, nb, s);
+    const bool vec = prolong_on_vector_unit(p == QMG_C128, t->nvec, nb);
+    if (p == QMG_C128) return prolong_t<double, double>(t, t->basis64, in, out, nb, vec, s);
+    if (t->storage == QMG_H16) return prolong_t<float, _Float16>(t, t->basis, in, out, nb, vec, s);
+    return prolong_t<float, float>(t, t->basis, in, out, nb, vec, s);
 }
 
 qmg_status transfer_restrict(qmg_transfer t, const void* in, void* out, qmg_prec p, int nb, hipStream_t s) {
-    if (one_member(t, p, nb)) {
-        if (p == QMG_C128) return restrict_one<double, cpx<double>, 1>(t, t->basis64, in, out, s);
-        if (t->nvec % 4 == 0) return restrict_one<float, uint32_t, 4>(t, t->basis, in, out, s);
-        if (t->nvec % 2 == 0) return restrict_one<float, uint32_t, 2>(t, t->basis, in, out, s);
-        return restrict_one<float, uint32_t, 1>(t, t->basis, in, out, s);
+    const bool h16 = t->storage == QMG_H16;
+    if (restrict_on_vector_unit(t, nb)) {
+        const int nv = t->nvec;
+        if (p == QMG_C128) return restrict_vec<double, cpx<double>, 1>(t, t->basis64, in, out, nb, s);
+        if (h16 && nv % 2 == 0) return restrict_vec<float, uint32_t, 2>(t, t->basis, in, out, nb, s);
+        if (h16) return restrict_vec<float, uint32_t, 1>(t, t->basis, in, out, nb, s);
+        if (nv % 2 == 0) return restrict_vec<float, cpx<float>, 2>(t, t->basis, in, out, nb, s);
+        return restrict_vec<float, cpx<float>, 1>(t, t->basis, in, out, nb, s);
     }
     if (p == QMG_C128) return restrict_t<double, double>(t, t->basis64, in, out, nb, s);
-    if (t->storage == QMG_H16) return restrict_t<float, _Float16>(t, t->basis, in, out, nb, s);
+    if (h16) return restrict_t<float, _Float16>(t, t->basis, in, out, nb, s);
     return restrict_t<float, float>(t, t->basis, in, out, nb, s);
 }
 }  // namespace qmg

@@ -205,3 +205,46 @@ def test_prolongation_error_is_that_of_short_chains(nvec, storage, cpc):
     e = {n: np.sqrt(v) for n, v in e.items()}
     print(nvec, storage, cpc, 'one %.3f batch %.3f' % (e['one'] / e['chains'], e['batch'] / e['chains']))
     assert e['one'] <= 1.03 * e['chains'] and e['batch'] <= 1.03 * e['chains'], e
+
+
+@pytest.mark.parametrize('storage', ['c64', 'c128', 'h16'])
+@pytest.mark.parametrize('dims,dof,block,nvec', [
+    ((4, 6, 2, 4), 12, (2, 3, 1, 2), 1),       # one vector: all members from one row of a thread
+    ((4, 4, 4, 6), 12, (2, 2, 2, 3), 2),
+    ((6, 6, 2, 2), 6, (3, 3, 1, 1), 3),        # three rows per site and chirality; rows end inside a chunk
+    ((4, 4, 4, 4), 12, (2, 2, 2, 2), 4),
+    ((4, 4, 4, 4), 12, (2, 2, 2, 2), 5),       # one run, not full
+    ((2, 4, 2, 2), 46, (1, 2, 1, 1), 10),      # fewer rows than the eight totals take
+    ((4, 4, 4, 6), 12, (2, 2, 2, 3), 12),
+    ((8, 8, 4, 4), 2, (4, 4, 2, 2), 13),       # one row per site and chirality
+    ((8, 8, 8, 16), 12, (4, 4, 4, 8), 24),     # more chunks than a work-group holds at a time
+    ((4, 4, 4, 8), 48, (2, 2, 2, 4), 26),
+    ((10, 6, 6, 8), 12, (5, 3, 3, 4), 33),
+    ((8, 8, 8, 8), 12, (4, 4, 4, 4), 64),      # the fewest chunks at a time
+])
+def test_a_member_of_any_batch_equals_the_single_transfer(dims, dof, block, nvec, storage):
+    """The vector-unit and the matrix-core forms sum in one order, so a member of a
+    batch equals its single call to the bit whatever form either takes: one, two,
+    four, nine and seventeen members, every storage.  The single calls against the
+    oracle (FP32 sums of at most a few thousand products 1e-5, FP64 1e-12), also
+    of complex128 fields with an FP16 basis."""
+    from paper_1612_07873_amd import Transfer
+    V = lattice.volume(dims)
+    vecs = synth.gaussian((nvec, V, dof), 11, 1)
+    Vb = transfer.block_orthonormalize(vecs, dims, block)
+    Vc = lattice.volume(transfer.coarse_dims(dims, block))
+    t = Transfer(dims, dof, block, dev(vecs), storage)
+    nrhs = 17
+    UC = np.stack([synth.gaussian((Vc, 2 * nvec), 60 + k, 2) for k in range(nrhs)])
+    F = np.stack([synth.gaussian((V, dof), 160 + k, 2) for k in range(nrhs)])
+    for cdt in {'c64': (torch.complex64,), 'c128': (torch.complex128,), 'h16': (torch.complex64, torch.complex128)}[storage]:
+        u, f = dev(UC, cdt), dev(F, cdt)
+        p, r = [t.prolong(u[k].contiguous()) for k in range(nrhs)], [t.restrict(f[k].contiguous()) for k in range(nrhs)]
+        Vr = _fp16_basis(Vb) if storage == 'h16' and cdt == torch.complex64 else Vb
+        tol = 1e-12 if cdt == torch.complex128 else 1e-5
+        assert rel_err(host(p[1]), transfer.prolong(Vr, UC[1], dims, block)) <= tol
+        assert rel_err(host(r[1]), transfer.restrict(Vr, F[1], dims, block)) <= tol
+        for m in (2, 4, 9, nrhs):
+            pm, rm = t.prolong(u[:m].contiguous()), t.restrict(f[:m].contiguous())
+            assert all(torch.equal(pm[k], p[k]) for k in range(m)), ('prolong', m)
+            assert all(torch.equal(rm[k], r[k]) for k in range(m)), ('restrict', m)
