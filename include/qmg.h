@@ -433,7 +433,8 @@ qmg_status qmg_transfer_export(qmg_transfer t, void* basis, void* stream);
 
 /* fine_out [nrhs][V][fine_dof] = P coarse_in [nrhs][Vc][N]; DEVICE fields,
  * precision p (QMG_C128, or QMG_C64 when the transfer was created with
- * QMG_C64); one launch covers every right-hand side; 1 <= nrhs <= 1024. */
+ * QMG_C64); one launch covers every right-hand side; 1 <= nrhs <= 1024.  Each
+ * right-hand side's result is bitwise that of a call with it alone. */
 qmg_status qmg_prolong(qmg_transfer t, const void* coarse_in, void* fine_out, int nrhs, qmg_prec p,
                        void* stream);
 

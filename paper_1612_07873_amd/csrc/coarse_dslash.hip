@@ -770,8 +770,9 @@ bool coarse_batch_uses_mfma(const qmg_coarse_op_s* op, int m) {
 // complex64).  A 16-bit operator with m in {8, 16, 32, 64} runs on the matrix
 // cores: the inputs are rounded to 16 bits with one scale per (site, member)
 // into q16 [V][m][N] / qsc [V][m] (caller-provided), then one multi-RHS launch
-// writes the complex64 outputs in place.  Otherwise one launch of the
-// single-RHS kernel covers all members (grid dimension y).
+// writes the complex64 outputs in place.  Otherwise one launch covers all
+// members: of the batched stencil where it has work-groups enough (use_batch),
+// else of the single-RHS kernel with the member in grid dimension y.
 qmg_status coarse_apply(qmg_coarse_op_s* op, const void* in, void* out, qmg_prec vprec, int m, void* q16,
                         float* qsc, hipStream_t s) {
     if (m > 1 && vprec == QMG_C64 && q16 && coarse_batch_uses_mfma(op, m)) {

@@ -20,7 +20,7 @@
 //
 // Several right-hand sides are solved together as a batch of nb members run
 // in lock step: every field of the batch is [member][site][component], each
-// kernel launch covers all members (grid dimension y), each member keeps its
+// kernel launch covers all members, each member keeps its
 // own scalars (its own Krylov space, step lengths and stopping test), and a
 // level's GCR stops when every member has reached its tolerance.  With a
 // 16-bit coarse operator and 8, 16, 32 or 64 members the coarse stencil runs

@@ -37,8 +37,10 @@ namespace qmg {
 
 // LF: storage of links and clover; VF: storage of the vectors (the same as LF
 // for complex128 / complex64, complex64 or 16-bit pairs for 16-bit links).
-// Grid dimension y runs over batch members: member b's fields follow the
-// first at b*V sites.
+// Member b of a batch finds its fields at b*V sites after the first's.  One
+// thread per site, grid dimension y over the members: the form for larger
+// lattices with few members, for 16-bit vectors and with DOT; the others run
+// one wave per hop direction (below; use_dirs chooses, both agree bitwise).
 // DOT: also the minimal-residual step's inner products of the result with
 // the input, <out,out> and <out,in> (re, im), summed over the work-group in
 // FP64 (fixed order) into part[member*pmember + value*pvalue + blockIdx.x].
@@ -272,15 +274,16 @@ __global__ __launch_bounds__(256) void k_wilson_clover(const void* __restrict__ 
 // in Eq. 2, its -1/2 included) the Schur complement on the even sites is
 //     S = C_ee - D_eo C_oo^-1 D_oe,
 // and M x = b is solved by S x_e = b_e - D_eo C_oo^-1 b_o followed by
-// x_o = C_oo^-1 (b_o - D_oe x_e).  Every piece is one launch of k_wilson_eo
-// over the sites x of one parity (half-lattice index h, x = hsite[h]):
+// x_o = C_oo^-1 (b_o - D_oe x_e).  Every piece is one launch of k_wilson_eo,
+// or of k_wilson_dirs (below; use_dirs chooses, both agree bitwise), over the
+// sites x of one parity (half-lattice index h, x = hsite[h]):
 //     out(x) = L_out( L_self(self(x)) + coef * [sum of the eight hops of hin](x) )
 // L_self: none (SELF 0), the identity (1) or C(x) (2); L_out: the identity or
 // C(x)^-1 (INV).  coef = 1 gives D, coef = -1 gives -D.  hin is a half-lattice
 // field of the other parity; the neighbour y of x has half index y >> 1,
 // because x0 runs fastest and L0 is even.  self and out are half-lattice
 // fields, or whole-lattice ones indexed by x (self_full, out_full).
-// Member b of a batch (grid dimension y) finds its fields at b*V/2 (half) or
+// Member b of a batch (grid dimension y of k_wilson_eo) finds its fields at b*V/2 (half) or
 // b*V (whole) sites.  Links, clover, inverse and neighbour table are read in
 // their parity-order copies: the thread of site x (parity p, half index h)
 // finds its own entries at p*V/2 + h and a neighbour y's link at
