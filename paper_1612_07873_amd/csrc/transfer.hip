@@ -1134,8 +1134,9 @@ static qmg_status restrict_vec(qmg_transfer t, const void* B, const void* in, vo
     // Non-temporal loads of a basis that the last-level cache (256 MB) does not hold, where rows neither share a
     // 64-byte sector nor are shorter than a cache line (one member, 4^4 blocks, with and without: 24^3x48 FP32 16
     // vectors 159 and 181 us, 24 246 and 268; 16^3x32 FP32 32, 403 MB, 65 and 75).  Elsewhere the cache serves what
-    // it holds (8^3x16 FP32 24 16.1 and 12.4 us), and sectors that rows share would be fetched again (24^3x48 FP32
-    // 20, 160 bytes, 246 and 221 us, FP16 24, 96 bytes, 176 and 145).
+    // it holds, to repeated calls (8^3x16 FP32 24 16.1 and 12.4 us) and to the prolongation after this one (in a
+    // solve on 16^3x32, FP32 24, 302 MB: restriction 57 and 68 us, prolongation 72 and 53); and sectors that rows
+    // share would be fetched again (24^3x48 FP32 20, 160 bytes, 246 and 221 us, FP16 24, 96 bytes, 176 and 145).
     const int row = t->nvec * (int)sizeof(BT);
     return row >= 128 && row % 64 == 0 && t->V * t->dof * row > 320000000 ? restrict_vec_t<R, BT, P, true>(t, B, in, out, nb, s)
                                                                           : restrict_vec_t<R, BT, P, false>(t, B, in, out, nb, s);

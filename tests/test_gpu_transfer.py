@@ -248,3 +248,21 @@ def test_a_member_of_any_batch_equals_the_single_transfer(dims, dof, block, nvec
             pm, rm = t.prolong(u[:m].contiguous()), t.restrict(f[:m].contiguous())
             assert all(torch.equal(pm[k], p[k]) for k in range(m)), ('prolong', m)
             assert all(torch.equal(rm[k], r[k]) for k in range(m)), ('restrict', m)
+
+
+@pytest.mark.parametrize('storage,nvec,sites', [
+    ('c64', 16, 104), ('c64', 16, 100), ('c128', 8, 104),   # rows of 128 bytes, either side of 320 MB
+])
+def test_one_member_restriction_of_a_large_basis(storage, nvec, sites):
+    """One member, either side of the rule that loads the basis past the cache: a
+    batch's member to the bit, the oracle to 1e-5 (FP32) and 1e-12 (FP64)."""
+    from paper_1612_07873_amd import Transfer
+    dims, block = (16, 16, 8, sites), (4, 4, 4, 4)
+    V = lattice.volume(dims)
+    g = torch.Generator('cuda').manual_seed(5)
+    cdt = torch.complex128 if storage == 'c128' else torch.complex64
+    t = Transfer(dims, 12, block, torch.randn(nvec, V, 12, generator=g, device='cuda', dtype=torch.complex128), storage)
+    f = torch.randn(2, V, 12, generator=g, device='cuda', dtype=cdt)
+    one, two = t.restrict(f[1].contiguous()), t.restrict(f)
+    assert torch.equal(one, two[1])
+    assert rel_err(host(one), transfer.restrict(host(t.basis()), host(f[1]), dims, block)) <= (1e-12 if storage == 'c128' else 1e-5)
